@@ -65,29 +65,20 @@ struct FusedLayout {
     int64_t sample;
 };
 
-// The sample whose workspace a call asks for: one to four select chunks, at
-// most a quarter of the bank.
-int64_t fused_sample_max(int64_t n) {
+// The sample: one to four select chunks, at most a quarter of the bank. Its
+// dense scan takes one row tile per block whatever its size up to a row tile
+// per CU, and a larger sample leaves fewer rows to the filtered scan and a
+// tighter bound (the 1M-row bank: 65,536 rows).
+int64_t fused_sample(int64_t n) {
     const int64_t chunk = is::select_chunk_len();
     const int64_t c = std::min<int64_t>(4, std::max<int64_t>(1, n / (4 * chunk)));
     return c * chunk;
 }
 
-// The sample a call takes when its workspace allows (a smaller one leaves more
-// survivor room to provide for): as few rows as leave about 2,048 survivors per
-// query, expected k (n - S) / S, in steps of 4,096 and no fewer than 4 k. The
-// filtered scan's time moves in whole row tiles per CU and hardly with the
-// sample. 1,024 queries, d = 768, k = 65, 50,021 rows: 4,096 rows take 21 us to
-// scan and 10 to rank, 16,384 rows four times that.
-int64_t fused_sample(int64_t n, int32_t k) {
-    const int64_t rows = std::max<int64_t>((int64_t)k * n / 2048, 4 * (int64_t)k);
-    const int64_t step = 4096;
-    return std::min(fused_sample_max(n), std::max<int64_t>(1, (rows + step - 1) / step) * step);
-}
-
-FusedLayout fused_layout(int64_t n, int32_t k, int32_t nq, int64_t S) {
+FusedLayout fused_layout(int64_t n, int32_t k, int32_t nq) {
     FusedLayout lay{};
-    const int64_t nch = (S + is::select_chunk_len() - 1) / is::select_chunk_len();
+    const int64_t S = fused_sample(n);
+    const int64_t nch = S / is::select_chunk_len();
     const int64_t gmax = is::mfma_max_blocks();
     lay.sample = S;
     size_t off = 0;
@@ -142,22 +133,23 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
         // chunk, then merged by rank), whose k-th key bounds the answer from
         // below; 3. the rest of the bank keeps only keys above it; 4. exact
         // ranking of sample winners + survivors
-        FusedLayout fl = fused_layout(n, k, nq, fused_sample(n, k));
-        if (fl.total > ws_bytes) fl = fused_layout(n, k, nq, fused_sample_max(n));
+        //
+        // Sample and rest are scored by one kernel: equal rows on either side
+        // of S then have equal scores, and the bound is a score of the kind it
+        // is compared with.
+        const FusedLayout fl = fused_layout(n, k, nq);
         const int64_t S = fl.sample;
         float* sc = (float*)(ws + fl.scores_off);
         uint64_t* first = (uint64_t*)(ws + fl.first_off);
         uint32_t* counts = (uint32_t*)(ws + fl.counts_off);
         uint64_t* regions = (uint64_t*)(ws + fl.regions_off);
         // the tile maxima of the sample live where the survivors go later
-        const int rows = dense_tile_rows(S, d, nq, 0, dtype);
+        const int rows = is::mfma_tile_rows();
         const bool tiles = is::select_tiles_applies(S, rows, k, nq);
         uint32_t* tmax = tiles ? (uint32_t*)regions : nullptr;
-        e = is::scan_direct_applies(S, d, nq, 0, dtype)
-                ? is::launch_scan_direct(query_emb, bank, S, d, nq, dtype, sc, tmax, st)
-                : is::launch_scan_mfma(query_emb, bank, d, nq, 0, S, sc, S, tmax, st);
+        e = is::launch_scan_mfma(query_emb, bank, d, nq, 0, S, sc, S, tmax, st);
         if (e != hipSuccess) return fail(IS_ERR_HIP, "scan launch: %s", hipGetErrorString(e));
-        const int nch = (int)((S + is::select_chunk_len() - 1) / is::select_chunk_len());
+        const int nch = (int)(S / is::select_chunk_len());
         if (tiles) {
             e = is::launch_select_tiles(sc, tmax, S, rows, k, nq, nullptr, nullptr, first, st);
         } else if (nch == 1) {
@@ -233,7 +225,7 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
 size_t retrieve_need(int64_t n, int32_t d, int32_t k, int32_t nq, int64_t bank_stride,
                      int32_t dtype) {
     return fused_applies(n, d, nq, bank_stride, dtype)
-               ? fused_layout(n, k, nq, fused_sample_max(n)).total
+               ? fused_layout(n, k, nq).total
                : retrieve_layout(n, k, nq).total;
 }
 
@@ -242,8 +234,7 @@ size_t retrieve_need(int64_t n, int32_t d, int32_t k, int32_t nq, int64_t bank_s
 size_t retrieve_want(int64_t n, int32_t d, int32_t k, int32_t nq, int32_t dtype) {
     size_t total = std::max(retrieve_layout(n, k, nq).total, dense_tiles_bytes(n, d, k, nq, 0, dtype));
     if (fused_applies(n, d, nq, 0, dtype))
-        total = std::max({total, fused_layout(n, k, nq, fused_sample_max(n)).total,
-                          fused_layout(n, k, nq, fused_sample(n, k)).total});
+        total = std::max(total, fused_layout(n, k, nq).total);
     return total;
 }
 

@@ -1384,15 +1384,8 @@ constexpr int kSelManyQueries = 512;
 hipError_t launch_select_scores(const float* scores, int64_t n, int k, int nq, int nchunks,
                                 uint64_t* cand, hipStream_t st) {
     dim3 grid((unsigned)nchunks, (unsigned)nq);
-    if (n <= 4 * kSelThreads && k <= 256 && nq >= kSelManyQueries)
-        hipLaunchKernelGGL((select_small_kernel<16, 256>), grid, dim3(256), 0, st, scores, n, k,
-                           (int32_t*)nullptr, (float*)nullptr, cand, nchunks);
-    else if (n <= 4 * kSelThreads)
-        hipLaunchKernelGGL((select_small_kernel<4>), grid, dim3(kSelThreads), 0, st, scores, n, k,
-                           (int32_t*)nullptr, (float*)nullptr, cand, nchunks);
-    else
-        hipLaunchKernelGGL((select_small_kernel<kSelKpt>), grid, dim3(kSelThreads), 0, st, scores,
-                           n, k, (int32_t*)nullptr, (float*)nullptr, cand, nchunks);
+    hipLaunchKernelGGL((select_small_kernel<kSelKpt>), grid, dim3(kSelThreads), 0, st, scores, n, k,
+                       (int32_t*)nullptr, (float*)nullptr, cand, nchunks);
     return hipGetLastError();
 }
 

@@ -204,6 +204,36 @@ def test_smaller_workspaces_give_the_same(n, d, nq, k, dt):
         assert torch.equal(sc.double(), o.values[:, :k])
 
 
+@pytest.mark.parametrize("n,d,nq", [(60_000, 768, 200), (100_000, 1024, 100), (400_000, 768, 40)])
+def test_filtered_scan_scores_equal_rows_equally(n, d, nq):
+    # each of 40 queries is a row of the sample that also stands among the rows
+    # after it: both copies score the same bits and the lower id comes first,
+    # also with k = 1, where the copy is dropped, and with the least workspace
+    g = torch.Generator(device="cuda").manual_seed(d + nq)
+    bank, q = _unit(n, d, g).to(torch.bfloat16), _unit(nq, d, g).to(torch.bfloat16)
+    first = torch.arange(40, device="cuda")
+    bank[n - 50 + first] = bank[first]
+    q[:40] = bank[first]
+    for k in (50, 1):
+        ids = torch.empty(nq, k, dtype=torch.int32, device="cuda")
+        sc = torch.empty(nq, k, device="cuda")
+
+        def call(ws):
+            is_retrieve(q, bank, n, d, k, ids, sc, nq=nq, workspace=ws)
+            torch.cuda.synchronize()
+
+        results = []
+        for size in (is_retrieve_workspace_size(n, d, k, nq, 1), _asked(call)):
+            call(torch.empty(size, dtype=torch.uint8, device="cuda"))
+            results.append((ids.clone(), sc.clone()))
+            assert torch.equal(ids[:40, 0].long(), first)
+            if k > 1:
+                assert torch.equal(ids[:40, 1].long(), n - 50 + first)
+                assert torch.equal(sc[:40, 0], sc[:40, 1])
+        assert torch.equal(results[0][0], results[1][0])
+        assert torch.equal(results[0][1], results[1][1])
+
+
 @pytest.mark.parametrize("n,R", [(1500, 20), (7000, 64), (40_000, 64)])
 def test_build_batches_give_the_same_graph(n, R):
     # batches of 1,024, of 512 and (the least workspace) of 256 rows; the last
