@@ -102,30 +102,36 @@ bool fused_applies(int64_t n, int32_t d, int32_t nq, int64_t bank_stride, int32_
 }
 
 // Rows per tile whose maxima the dense scan of these sizes can write beside the
-// scores (0: none).
-int dense_tile_rows(int64_t n, int32_t d, int32_t nq, int64_t bank_stride, int32_t dtype) {
-    if (is::scan_direct_applies(n, d, nq, bank_stride, dtype)) return is::scan_direct_tile_rows(n, nq);
-    return is::scan_mfma_applies(n, d, nq, bank_stride, dtype) ? is::mfma_tile_rows() : 0;
+// scores (0: none). `plan`: see enqueue_retrieve.
+int dense_tile_rows(int64_t n, int32_t d, int32_t plan, int64_t bank_stride, int32_t dtype) {
+    if (is::scan_direct_applies(n, d, plan, bank_stride, dtype))
+        return is::scan_direct_tile_rows(n, plan);
+    return is::scan_mfma_applies(n, d, plan, bank_stride, dtype) ? is::mfma_tile_rows() : 0;
 }
 
 // Workspace with which a dense scan's scores are ranked from the maxima of its
 // tiles (they take the place of the chunk winners); 0: that never applies.
 size_t dense_tiles_bytes(int64_t n, int32_t d, int32_t k, int32_t nq, int64_t bank_stride,
-                         int32_t dtype) {
-    const int rows = dense_tile_rows(n, d, nq, bank_stride, dtype);
+                         int32_t dtype, int32_t plan) {
+    const int rows = dense_tile_rows(n, d, plan, bank_stride, dtype);
     if (rows == 0 || !is::select_tiles_applies(n, rows, k, nq)) return 0;
     const int64_t tiles = (n + rows - 1) / rows;
     return retrieve_layout(n, k, nq).cand_a_off + (size_t)nq * (size_t)tiles * sizeof(uint32_t);
 }
 
 // Enqueues the retrieval kernels (arguments already validated, workspace of
-// ws_bytes, at least retrieve_need).
+// ws_bytes, at least retrieve_need). The scan that scores the rows is the one
+// for `plan` queries: each sums in an order of its own, and a caller that hands
+// its queries over in parts gives every part the same plan, so that a query's
+// scores do not depend on the parts (plan >= 2 implies a shared bank).
 int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t d, int32_t k,
                      int32_t* out_ids, float* out_scores, int32_t nq, int64_t bank_stride,
-                     int32_t dtype, void* workspace, size_t ws_bytes, hipStream_t st) {
+                     int32_t dtype, void* workspace, size_t ws_bytes, hipStream_t st,
+                     int32_t plan) {
     const RetrieveLayout lay = retrieve_layout(n, k, nq);
-    const bool direct = is::scan_direct_applies(n, d, nq, bank_stride, dtype);
-    const bool fused = !direct && fused_applies(n, d, nq, bank_stride, dtype);
+    const bool direct = is::scan_direct_applies(n, d, plan, bank_stride, dtype);
+    const bool mfma = !direct && is::scan_mfma_applies(n, d, plan, bank_stride, dtype);
+    const bool fused = mfma && fused_applies(n, d, nq, bank_stride, dtype);
     char* ws = (char*)workspace;
     hipError_t e;
     if (fused) {
@@ -173,15 +179,15 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
         return ok();
     }
     float* scores = (float*)(ws + lay.scores_off);
-    const size_t tiles_bytes = dense_tiles_bytes(n, d, k, nq, bank_stride, dtype);
+    const size_t tiles_bytes = dense_tiles_bytes(n, d, k, nq, bank_stride, dtype, plan);
     uint32_t* tmax = tiles_bytes && ws_bytes >= tiles_bytes ? (uint32_t*)(ws + lay.cand_a_off) : nullptr;
-    e = direct ? is::launch_scan_direct(query_emb, bank, n, d, nq, dtype, scores, tmax, st)
-        : is::scan_mfma_applies(n, d, nq, bank_stride, dtype)
+    e = direct ? is::launch_scan_direct(query_emb, bank, n, d, nq, plan, dtype, scores, tmax, st)
+        : mfma
             ? is::launch_scan_mfma(query_emb, bank, d, nq, 0, n, scores, n, tmax, st)
             : is::launch_scan(query_emb, bank, n, d, nq, bank_stride, dtype, scores, st);
     if (e != hipSuccess) return fail(IS_ERR_HIP, "scan launch: %s", hipGetErrorString(e));
     if (tmax) {
-        e = is::launch_select_tiles(scores, tmax, n, dense_tile_rows(n, d, nq, bank_stride, dtype),
+        e = is::launch_select_tiles(scores, tmax, n, dense_tile_rows(n, d, plan, bank_stride, dtype),
                                     k, nq, out_ids, out_scores, nullptr, st);
         if (e != hipSuccess) return fail(IS_ERR_HIP, "select launch: %s", hipGetErrorString(e));
         return ok();
@@ -231,8 +237,9 @@ size_t retrieve_need(int64_t n, int32_t d, int32_t k, int32_t nq, int64_t bank_s
 
 // Workspace with which it takes its fastest path (the bank layout is not known
 // where it is asked for: a shared bank).
-size_t retrieve_want(int64_t n, int32_t d, int32_t k, int32_t nq, int32_t dtype) {
-    size_t total = std::max(retrieve_layout(n, k, nq).total, dense_tiles_bytes(n, d, k, nq, 0, dtype));
+size_t retrieve_want(int64_t n, int32_t d, int32_t k, int32_t nq, int32_t dtype, int32_t plan) {
+    size_t total = std::max(retrieve_layout(n, k, nq).total,
+                            dense_tiles_bytes(n, d, k, nq, 0, dtype, plan));
     if (fused_applies(n, d, nq, 0, dtype))
         total = std::max(total, fused_layout(n, k, nq).total);
     return total;
@@ -253,17 +260,19 @@ constexpr size_t kAnnBuildBytes = (size_t)1 << 30;
 
 struct AnnBuildLayout {
     int batch;
+    int plan;  // queries that every batch's scan is chosen for
     size_t ids_off, fwd_off, merge_off, total;
 };
 
 AnnBuildLayout ann_build_layout(int64_t n, int32_t d, int32_t R, int32_t dtype, int batch) {
     AnnBuildLayout lay{};
     lay.batch = (int)std::min<int64_t>(batch, n);
+    lay.plan = (int)std::min<int64_t>(kAnnBuildBatch, n);
     const int last = (int)(n - (n - 1) / lay.batch * lay.batch);
     // (the smallest batch asks for what its retrieval has to have, so what a
     // workspace of that size serves stays as it is)
     auto bytes = [&](int nq) {
-        return batch > kAnnBuildBatch ? retrieve_want(n, d, R + 1, nq, dtype)
+        return batch > kAnnBuildBatch ? retrieve_want(n, d, R + 1, nq, dtype, lay.plan)
                                       : retrieve_need(n, d, R + 1, nq, 0, dtype);
     };
     size_t off = round_up(std::max(bytes(lay.batch), bytes(last)), 256);
@@ -442,7 +451,7 @@ int is_retrieve_workspace_size(int64_t n, int32_t d, int32_t k, int32_t nq, int3
     *bytes = 0;
     const int rc = check_retrieve_sizes(n, d, k, nq, dtype);
     if (rc) return rc;
-    *bytes = retrieve_want(n, d, k, nq, dtype);
+    *bytes = retrieve_want(n, d, k, nq, dtype, nq);
     return ok();
 }
 
@@ -459,7 +468,7 @@ int is_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t d, i
     if (!aligned(workspace, 256)) return fail(IS_ERR_INVALID, "workspace must be 256-byte aligned");
 
     return enqueue_retrieve(query_emb, bank, n, d, k, out_ids, out_scores, nq, bank_stride, dtype,
-                            workspace, workspace_bytes, (hipStream_t)stream);
+                            workspace, workspace_bytes, (hipStream_t)stream, nq);
 }
 
 int is_retrieve_noalloc(const void* query_emb, const void* bank, int64_t n, int32_t d, int32_t k,
@@ -480,7 +489,7 @@ int is_retrieve_noalloc(const void* query_emb, const void* bank, int64_t n, int3
     // every retrieval kernel writes the scratch it later reads: nothing in it
     // has to start at zero
     return enqueue_retrieve(query_emb, bank, n, d, k, out_ids, out_scores, nq, bank_stride, dtype,
-                            ws, kNoAllocScratchBytes, (hipStream_t)stream);
+                            ws, kNoAllocScratchBytes, (hipStream_t)stream, nq);
 }
 
 int is_stream_copy(void* dst, const void* src, size_t bytes, void* stream) {
@@ -714,7 +723,7 @@ int is_ann_build(const void* bank, int64_t n, int32_t d, int32_t degree, int32_t
         const int nb = (int)std::min<int64_t>(lay.batch, n - row0);
         const void* rows = (const char*)bank + (size_t)row0 * d * esize;
         rc = enqueue_retrieve(rows, bank, n, d, degree + 1, ids, nullptr, nb, 0, dtype, ws,
-                              lay.ids_off, st);
+                              lay.ids_off, st, lay.plan);
         if (rc) return rc;
         hipError_t e = is::launch_ann_take(ids, row0, nb, degree, F, st);
         if (e != hipSuccess) return fail(IS_ERR_HIP, "graph build launch: %s", hipGetErrorString(e));
@@ -790,7 +799,7 @@ int is_ann_search(const void* query_emb, int32_t nq, const void* bank, int64_t n
     int32_t* init_ids = (int32_t*)(ws + lay.ids_off);
     float* init_scores = (float*)(ws + lay.scores_off);
     rc = enqueue_retrieve(query_emb, seed_bank, n_seeds, d, lay.n_init, init_ids, init_scores, nq,
-                          0, dtype, ws, lay.ids_off, st);
+                          0, dtype, ws, lay.ids_off, st, nq);
     if (rc) return rc;
     hipError_t e = is::launch_ann_search(query_emb, nq, bank, n, d, dtype, graph, degree, seed_ids,
                                          n_seeds, init_ids, init_scores, lay.n_init, beam, width,

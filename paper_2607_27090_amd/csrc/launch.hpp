@@ -35,11 +35,12 @@ hipError_t launch_scan_mfma_filter(const void* query, const void* bank, int d, i
                                    int k, uint64_t* regions, uint32_t* counts, hipStream_t st);
 // scan_direct.hip: several queries on one shared bank, dense scores
 // scores[q * n + row]; with tmax also the largest score of every
-// scan_direct_tile_rows() rows, as order bits, tmax[q][tiles].
+// scan_direct_tile_rows() rows, as order bits, tmax[q][tiles]. Tile and sums are
+// those for `plan` queries, whatever nq.
 bool scan_direct_applies(int64_t n, int d, int nq, int64_t bank_stride, int dtype);
-int scan_direct_tile_rows(int64_t n, int nq);
+int scan_direct_tile_rows(int64_t n, int plan);
 hipError_t launch_scan_direct(const void* query, const void* bank, int64_t n, int d, int nq,
-                              int dtype, float* scores, uint32_t* tmax, hipStream_t st);
+                              int plan, int dtype, float* scores, uint32_t* tmax, hipStream_t st);
 int64_t select_chunk_len();
 // The k winners of each select_chunk_len() chunk of fp32 scores [nq][n], as
 // keys best first and 0-padded, to cand[q][chunk][k].

@@ -260,6 +260,33 @@ def test_build_batches_give_the_same_graph(n, R):
         assert torch.equal(first[i, :R // 2].long(), f)
 
 
+@pytest.mark.parametrize("n,d,dt", [
+    (700, 768, torch.bfloat16),      # 256 rows: tiles of 16 x 16, their sums in eight parts
+    (1300, 200, torch.float32),      # last batches of 20 and 276 rows
+    (7000, 768, torch.bfloat16),     # 1,024 rows would be past the direct scan's bound
+    (33_044, 264, torch.bfloat16),   # filtered; last batches of 20 and 276 rows
+])
+def test_build_does_not_depend_on_the_workspace(n, d, dt):
+    # real-valued rows: every batch size scores a row in the same order of sums,
+    # so the graph is the same bit for bit; rows that stand twice tie exactly
+    g = torch.Generator(device="cuda").manual_seed(n)
+    R = 48
+    bank = _unit(n, d, g).to(dt)
+    bank[n // 2:n // 2 + 200] = bank[:200]
+
+    def call(ws):
+        out = torch.full((n, R), -1, dtype=torch.int32, device="cuda")
+        is_ann_build(bank, n, d, R, out, workspace=ws)
+        torch.cuda.synchronize()
+        return out
+
+    want = is_ann_build_workspace_size(n, d, R, 0 if dt == torch.float32 else 1)
+    first = call(torch.empty(want, dtype=torch.uint8, device="cuda"))
+    for size in (want - 256, _asked(call)):
+        assert torch.equal(call(torch.empty(size, dtype=torch.uint8, device="cuda")), first)
+    assert torch.equal(first[:200, 0].long(), n // 2 + torch.arange(200, device="cuda"))
+
+
 @pytest.mark.parametrize("n,d,nq,dt", [(60, 4104, 1, torch.float32), (60, 8192, 1, torch.float32),
                                        (60, 8192, 3, torch.float32), (60, 8192, 1, torch.bfloat16)])
 def test_longest_rows(n, d, nq, dt):
