@@ -102,6 +102,32 @@ def test_direct_scan_non_finite_operands(dt):
         assert (np.abs(s[fin].astype(np.float64) - e[fin]) <= 2.0 ** -20 * mag[fin]).all()
 
 
+@pytest.mark.parametrize("small,large", [
+    (1.2345e-36, 1e35), (1.2e-38, 1e35), (3e-41, 1e38), (1e-36, 1.0), (1e-31, 1e30), (1e-29, 1e28)])
+@pytest.mark.parametrize("swap", [False, True])
+def test_direct_scan_tiny_operands(small, large, swap):
+    # operands whose lower bf16 parts are cut short or lost, against large ones:
+    # what is lost then counts. Rows 0 to 9 hold tiny values only, 10 to 19 a few
+    # among ordinary ones, 20 is zero. fp32 products of d terms: d roundings.
+    g = torch.Generator(device="cuda").manual_seed(9)
+    n, d, nq = 70, 72, 19
+    a, b = torch.rand(n, d, generator=g, device="cuda") + 1, torch.rand(nq, d, generator=g, device="cuda") + 1
+    a[:10] *= small
+    a[10:20, 3:7] *= small
+    a[10:20, 7:] = 0
+    a[20] = 0
+    b *= large
+    if swap:
+        a, b, n, nq = b, a, nq, n
+    gids, gsc = _retrieve(b, a, n)
+    p = b.double().cpu().numpy()[:, None, :] * a.double().cpu().numpy()[None, :, :]
+    ids = gids.astype(np.int64)
+    e = np.take_along_axis(p.sum(-1), ids, axis=1)
+    mag = np.take_along_axis(np.abs(p).sum(-1), ids, axis=1)
+    fin = e <= 3.4e38
+    assert (np.abs(gsc[fin].astype(np.float64) - e[fin]) <= d * 2.0 ** -24 * mag[fin] + d * 2.0 ** -149).all()
+
+
 @pytest.mark.parametrize("n,d,nq,k", [
     (16_385, 16, 9, 100),       # 32-row tiles: 513 maxima, one per thread; a last tile of one row
     (20_011, 72, 64, 50),       # 64-row tiles
