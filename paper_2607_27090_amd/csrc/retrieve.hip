@@ -1216,9 +1216,16 @@ __device__ int select_stream(Load&& load, int64_t total, int k, SelShared& sh) {
 // `rows` rows, tmax[q][T] (score order bits), one block per query. At least
 // `want` tile maxima are >= tau, so at least `want` scores are, and a score >=
 // tau lies in a tile whose maximum is: only those tiles (want and a few) are
-// read, instead of the whole row. Their scores >= tau are ranked pairwise;
-// when there are more than kSelRankMax (ties), or more tiles than one block
-// holds, the whole row is ranked in chunks.
+// read, instead of the whole row, and their scores >= tau are ranked, pairwise
+// or by the radix select.
+//
+// Where the quick bound leaves too much (many equal maxima; want near the number
+// of threads, whose maxima the bound is taken from), the tiles themselves are
+// ranked, by maximum and then by position: the `want` first hold the answer (a
+// row outside them has, in each of them, one that scores more, or as much at a
+// lower id), and the last one's maximum is the bound. What still exceeds the
+// candidates' memory then (equal scores) is ranked in chunks, want * rows keys at
+// most.
 // Bound: latency, two dependent reads and the bound's barriers. 8 rows of
 // 100,000 scores, k = 100: 7.9 us, against 9.5 + 5.8 us for the chunk winners
 // and their merge; 64 rows of 20,011, k = 50: 7.5 against 11.2 + 5.2 us (the
@@ -1250,7 +1257,7 @@ __global__ __launch_bounds__(kSelThreads) void select_tiles_kernel(
         tm = max(tm, u[i]);
     }
     const int want = (int)min_i64(k, n);  // <= min(T, kSelThreads)
-    const uint32_t tau = bound_from_maxima(tm, t < T, want, sh, s_hist2);
+    uint32_t tau = bound_from_maxima(tm, t < T, want, sh, s_hist2);
 
 #pragma unroll
     for (int i = 0; i < KPT; ++i) {
@@ -1264,10 +1271,11 @@ __global__ __launch_bounds__(kSelThreads) void select_tiles_kernel(
         }
     }
     __syncthreads();
-    const uint32_t ntile = s_ntile;
-    bool few = ntile <= (uint32_t)kSelTiles;
-    if (few) {
-        const int total = (int)ntile * rows;
+    // (twice `want` tiles and some: more than the bound leaves unless maxima tie
+    // or `want` nears the thread count)
+    int ntile = (int)s_ntile;
+    auto gather = [&]() {
+        const int total = ntile * rows;
         constexpr int kAhead = 4;
         for (int e0 = 0; e0 < total; e0 += kAhead * kSelThreads) {
             float sv[kAhead];
@@ -1289,19 +1297,55 @@ __global__ __launch_bounds__(kSelThreads) void select_tiles_kernel(
                     uint32_t at = 0;
                     if (lane == 0) at = atomicAdd(&s_ncand, (uint32_t)__popcll(mask));
                     at = __shfl(at, 0, kWave) + lanes_below(mask);
-                    if (in && at < (uint32_t)kSelRankMax)
+                    if (in && at < (uint32_t)kSelCap)
                         sh.cand[at] = ((uint64_t)bits << 32) | (uint64_t)(~(uint32_t)id[i]);
                 }
             }
         }
         __syncthreads();
-        few = s_ncand <= (uint32_t)kSelRankMax;
+    };
+    bool quick = ntile <= min(2 * want + 64, kSelTiles);
+    if (quick) {
+        gather();
+        quick = s_ncand <= (uint32_t)kSelCap;
     }
+    if (__builtin_expect(!quick, 0)) {
+        uint64_t tk[KPT];
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) {
+            const int x = t + i * kSelThreads;
+            tk[i] = x < T ? ((uint64_t)u[i] << 32) | (uint64_t)(~(uint32_t)x) : 0ull;
+        }
+        select_block(tk, want, sh);  // (T >= want)
+        if (t < want) s_tile[t] = (int32_t)key_id(sh.sel[t]);
+        if (t == 0) s_ncand = 0;
+        tau = (uint32_t)(sh.sel[want - 1] >> 32);
+        ntile = want;
+        __syncthreads();
+        gather();
+    }
+    const uint32_t ncand = s_ncand;
     int got = want;
-    if (few)
-        rank_candidates(s_ncand, want, sh);
-    else
-        got = select_stream<8>([&](int64_t x) { return rank_key(sq[x], (uint32_t)x); }, n, k, sh);
+    if (ncand <= (uint32_t)kSelRankMax) {
+        rank_candidates(ncand, want, sh);
+    } else if (ncand <= (uint32_t)kSelCap) {
+        uint64_t key[kSelCap / kSelThreads];
+#pragma unroll
+        for (int i = 0; i < kSelCap / kSelThreads; ++i) {
+            const uint32_t x = t + i * kSelThreads;
+            key[i] = x < ncand ? sh.cand[x] : 0ull;
+        }
+        // (every candidate is read before select_block's first barrier, and it
+        // writes them again only after that)
+        got = select_block(key, k, sh);
+    } else {
+        got = select_stream<8>(
+            [&](int64_t x) {
+                const int64_t row = (int64_t)s_tile[(int)x / rows] * rows + (int)x % rows;
+                return row < n ? rank_key(sq[row], (uint32_t)row) : 0ull;
+            },
+            (int64_t)ntile * rows, k, sh);
+    }
 
     if (out_keys) {
         for (int i = t; i < k; i += kSelThreads)
