@@ -21,4 +21,39 @@ inline GridXY fold_grid(int64_t blocks, int threads) {
     return y <= 65535 ? GridXY{(uint32_t)x, (uint32_t)y} : GridXY{0, 0};
 }
 
+struct RowShares {
+    int blocks;    // per query tile, at most `cus`
+    int64_t rows;  // rows of one, a multiple of `step`
+};
+
+// Shares of `rows` rows, walked in tiles of `tile`, for each of `qtiles` query
+// tiles, one block per CU at a time. One round of blocks over all query tiles,
+// so that a block walks several row tiles and its loads run on across them
+// (1,024 queries over 45,925 rows, d = 768: 64 x 4 blocks of three tiles 94 us,
+// 180 x 4 of one 111); more rounds of smaller shares where one leaves too many
+// CUs without a block (129 query tiles: 129 of 256). A round costs its largest
+// share's tiles and about a quarter of one to start.
+inline RowShares row_shares(int64_t rows, int tile, int step, int qtiles, int cus) {
+    const int64_t tiles = (rows + tile - 1) / tile;
+    RowShares best{1, 0};
+    double least = 0;
+    for (int round = 1; round <= 8; ++round) {
+        int64_t g = (int64_t)round * cus / qtiles;
+        if (g < 1) g = 1;
+        if (g > cus) g = cus;
+        if (g > tiles) g = tiles;
+        if (g < 1) g = 1;
+        int64_t share = (rows + g - 1) / g;
+        share = (share + step - 1) / step * step;
+        const int64_t rounds = (g * qtiles + cus - 1) / cus;
+        const double cost = (double)rounds * ((double)((share + tile - 1) / tile) + 0.25);
+        if (best.rows == 0 || cost < least) {
+            best = {(int)g, share};
+            least = cost;
+        }
+        if (qtiles == 1) break;
+    }
+    return best;
+}
+
 }  // namespace is

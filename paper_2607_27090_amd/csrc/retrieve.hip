@@ -25,8 +25,9 @@
 //     bounds those); the survivors of the filtered matrix-core scan are
 //     ranked by select_regions_kernel. Ties go to the lower id (score desc,
 //     id asc).
-#include "wave.hpp"
+#include "grid.hpp"
 #include "launch.hpp"
+#include "wave.hpp"
 
 namespace is {
 
@@ -598,20 +599,11 @@ bool scan_mfma_applies(int64_t n, int d, int nq, int64_t bank_stride, int dtype)
     return dtype == IS_DTYPE_BF16 && bank_stride == 0 && nq >= 32 && d >= 64;
 }
 
-// One block per CU over all query tiles, so that with several of them a block
-// walks several row tiles and its loads run on across them (1,024 queries over
-// 45,925 rows, d = 768: 64 x 4 blocks of three tiles 94 us, 180 x 4 of one 111).
 void mfma_grid(int64_t rows, int nq, int* blocks, int64_t* rows_per_block) {
-    int64_t g = (rows + kMmRows - 1) / kMmRows;
-    const int nqt = (nq + kMmQ - 1) / kMmQ;
-    const int64_t cus = compute_units() < kMmMaxBlocks ? compute_units() : kMmMaxBlocks;
-    const int64_t cap = cus / nqt > 1 ? cus / nqt : 1;
-    if (g > cap) g = cap;
-    if (g < 1) g = 1;
-    int64_t rpb = (rows + g - 1) / g;
-    rpb = (rpb + 31) / 32 * 32;
-    *blocks = (int)g;
-    *rows_per_block = rpb;
+    const int cus = compute_units() < kMmMaxBlocks ? compute_units() : kMmMaxBlocks;
+    const RowShares g = row_shares(rows, kMmRows, 32, (nq + kMmQ - 1) / kMmQ, cus);
+    *blocks = g.blocks;
+    *rows_per_block = g.rows;
 }
 
 int mfma_max_blocks() { return kMmMaxBlocks; }

@@ -15,6 +15,11 @@ extern "C" void fold(int64_t blocks, int threads, uint32_t* xy) {
     xy[0] = g.x;
     xy[1] = g.y;
 }
+extern "C" int64_t shares(int64_t rows, int qtiles, int cus, int* blocks) {
+    const is::RowShares g = is::row_shares(rows, 256, 32, qtiles, cus);
+    *blocks = g.blocks;
+    return g.rows;
+}
 """
 
 
@@ -51,3 +56,21 @@ def test_folded_grids_hold_every_block(lib, blocks, threads):
 
 def test_blocks_past_a_grid_are_refused(lib):
     assert _fold(lib, 2 ** 41, 256) == (0, 0)
+
+
+@pytest.mark.parametrize("rows", [1, 255, 256, 500, 3000, 16_384, 45_925, 100_000, 934_464])
+def test_row_shares_keep_the_cus_busy(lib, rows):
+    lib.shares.restype = ctypes.c_int64
+    cus, tiles = 256, -(-rows // 256)
+    for qtiles in [1, 2, 3, 4, 5, 7, 16, 65, 100, 127, 128, 129, 160, 170, 200, 255, 256]:
+        b = ctypes.c_int()
+        share = lib.shares(ctypes.c_int64(rows), qtiles, cus, ctypes.byref(b))
+        blocks = b.value
+        assert share % 32 == 0 and 1 <= blocks <= min(cus, tiles) and blocks * share >= rows
+        if qtiles == 1:
+            assert blocks == min(cus, tiles)
+        # row tiles one CU after the other has to take, against an even split of
+        # all tiles over all CUs (a block takes whole tiles: at most one more)
+        walk = -(-blocks * qtiles // cus) * -(-share // 256)
+        even = tiles * qtiles / cus
+        assert walk <= 1.34 * even + 1, (qtiles, blocks, share, walk, even)
