@@ -126,3 +126,31 @@ def test_paged_scores_non_finite_operands():
     assert ((sc[0, :4, 4].double() - e).abs() <= 64 * 2.0 ** -24 * e).all()
     assert not torch.isfinite(sc[0, 7]).any()
     assert torch.isfinite(sc[0, :4, 5:]).all()
+
+
+@pytest.mark.parametrize("D", [16, 32, 64, 128, 256, 512])
+def test_paged_scores_precision(D):
+    # against 64 bits no further off than fp32 multiply-adds over eight elements,
+    # added pairwise (emulated; the query's rotation rounds in both)
+    bt, pk, q, m = _setup(6, 8, 2, D, 640, 16, 0, seed=D)
+    sc, st = _run(bt, pk, q, m, 640, 16, 0, 0, False)
+    assert st == 0
+    off = [0.0, 0.0, 0.0]
+    f = THETA ** (-torch.arange(0, D, 2, dtype=torch.float64, device="cuda") / D)
+    for r in range(6):
+        ref, _, slot = _reference(bt, pk, q, m, 16, 0, 0, False, r)
+        n = int(m[r])
+        a = (float(n) * f).remainder(2 * np.pi).float()
+        c, s, x, h = a.cos(), a.sin(), q[r].float(), D // 2
+        y = torch.cat([x[:, :h] * c - x[:, h:] * s, x[:, h:] * c + x[:, :h] * s], -1)
+        p = y.view(1, 8, D // 8, 8) * pk[0][slot].float().repeat_interleave(4, 1).view(n, 8, D // 8, 8)
+        t = p[..., 0]
+        for e in range(1, 8):
+            t = t + p[..., e]
+        while t.shape[-1] > 1:
+            t = t[..., ::2] + t[..., 1::2]
+        off[0] += float((sc[r, :, :n].double() - ref).square().sum())
+        off[1] += float((t[..., 0].t().double() - ref).square().sum())
+        off[2] += float(ref.square().sum())
+    ours, theirs = (off[0] / off[2]) ** 0.5, (off[1] / off[2]) ** 0.5
+    assert ours <= theirs, (ours, theirs)
