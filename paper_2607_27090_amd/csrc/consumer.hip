@@ -12,7 +12,7 @@
 //     three of the four rows of each query head and are added at the end,
 //     smallest first. Products are exact, sums fp32, of at most 128 elements
 //     each: relative error (2-norm) against 64 bits for D = 16 / 64 / 128 / 256 /
-//     512: @ERR@e-8, where one fp32 multiply-add per element summed over
+//     512: 6.0 / 7.7 / 8.6 / 9.0 / 9.4e-8, where one fp32 multiply-add per element summed over
 //     D / 8 lanes gives 7.9 / 9.3 / 9.5 / 10.0 / 10.3e-8.
 //   * one block per (share of the tokens, share of the heads, request): it maps
 //     its tokens to slots, rotates its query heads to qpos[r] (one sine and
