@@ -21,9 +21,11 @@
 //     (whole 128-byte lines), turns them into fragments through a part of LDS
 //     of its own, and has the next item's loads in flight while it multiplies:
 //     no barriers in the loop.
-//   * a logit that comes out non-finite, or below 2^-90 (where the parts of
-//     either operand may not be defined or cut short), is formed again in fp32
-//     from the operands.
+//   * a logit that comes out non-finite (an infinite or NaN operand, or a rotated
+//     one past the largest bf16, has no split), and every logit of a query head
+//     with a rotated element below 2^-100 (below 2^-110 the smallest bf16,
+//     2^-133, cuts its lower parts short), is formed again in binary64 from the
+//     fp32 rotation of the query in memory.
 // Bound: the keys' bytes, and the set-up (two dependent round trips before the
 // first key is asked for). 32 requests of 1,280-2,560 tokens, 32 / 8 heads of
 // 128, 134 MB: 30.5 us = 4.4 TB/s; summing with fp32 multiply-adds, the query
@@ -48,6 +50,8 @@ constexpr int kConsMaxTokens = 512; // tokens per block at most
 // 36.7 / 33.5 / 40.5 / 35.7 us.
 constexpr int kConsBlocksPerCu = 4;
 constexpr int kConsQBytes = 13 << 10;
+constexpr int kConsMaxHeads = kConsQBytes / (16 * 6);  // query heads of a block (D = 16)
+static_assert(kConsMaxHeads >= kConsMaxG, "one KV head's query heads");
 
 typedef __bf16 bf16x8_c __attribute__((ext_vector_type(8)));
 typedef float f32x4_c __attribute__((ext_vector_type(4)));
@@ -63,9 +67,16 @@ __device__ __forceinline__ uint4 load_key(const uint4* p) {
 struct ConsShared {
     int64_t slot[kConsMaxTokens];  // slot of each token of the block, -1: skipped
     float cs[IS_MAX_HEAD_DIM / 2], sn[IS_MAX_HEAD_DIM / 2];
+    int32_t tiny[kConsMaxHeads];  // a query head's split may be cut short
     uint32_t flags;
-    int32_t any_bad;
+    int32_t any_bad, any_tiny;
 };
+
+// A pair of query elements rotated by its angle.
+__device__ __forceinline__ float2 rotate_pair(uint16_t e0, uint16_t e1, float cs, float sn) {
+    const float x0 = __uint_as_float((uint32_t)e0 << 16), x1 = __uint_as_float((uint32_t)e1 << 16);
+    return make_float2(fmaf(x0, cs, -(x1 * sn)), fmaf(x1, cs, x0 * sn));
+}
 
 // DC: head elements per step (min(D, 128)); RT: 4-head tiles (G <= 4 RT).
 template <int DC, int RT>
@@ -98,7 +109,8 @@ __global__ __launch_bounds__(kConsThreads) void paged_scores_kernel(
     const int half = D >> 1;
 
     // ---- slots of the block's tokens; sine and cosine of every pair ----
-    if (t == 0) { sh.flags = 0; sh.any_bad = 0; }
+    if (t == 0) { sh.flags = 0; sh.any_bad = 0; sh.any_tiny = 0; }
+    for (int i = t; i < nh * G; i += kConsThreads) sh.tiny[i] = 0;
     __syncthreads();
     const int32_t* btr = block_table + (int64_t)r * max_blocks;
     uint32_t flags = 0;
@@ -169,10 +181,10 @@ __global__ __launch_bounds__(kConsThreads) void paged_scores_kernel(
         const int hq = i / half, j = i - hq * half;
         const int i0 = hq * D + (interleaved ? 2 * j : j);
         const int i1 = hq * D + (interleaved ? 2 * j + 1 : j + half);
-        const float cs = sh.cs[j], sn = sh.sn[j];
-        const float x0 = __uint_as_float((uint32_t)qr[i0] << 16);
-        const float x1 = __uint_as_float((uint32_t)qr[i1] << 16);
-        float y0 = fmaf(x0, cs, -(x1 * sn)), y1 = fmaf(x1, cs, x0 * sn);
+        const float2 y = rotate_pair(qr[i0], qr[i1], sh.cs[j], sh.sn[j]);
+        float y0 = y.x, y1 = y.y;
+        if ((y0 != 0.f && fabsf(y0) < 0x1p-100f) || (y1 != 0.f && fabsf(y1) < 0x1p-100f))
+            sh.tiny[hq] = sh.any_tiny = 1;
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
             const uint32_t w = pack_bf16x2(y0, y1);
@@ -183,6 +195,8 @@ __global__ __launch_bounds__(kConsThreads) void paged_scores_kernel(
         }
     }
     __syncthreads();
+
+    const bool any_tiny = sh.any_tiny != 0;
 
     // matrix row 4 g' + p of tile rt: part p of query head 4 rt + g' (p = 3
     // and heads past G: zero)
@@ -246,18 +260,17 @@ __global__ __launch_bounds__(kConsThreads) void paged_scores_kernel(
             if (gq >= G || slot < 0) continue;
             const f32x4_c sum = DC < 128 ? acc[rt] : done[rt] + acc[rt];
             float s = (sum[2] + sum[1]) + sum[0];
-            const float mag = fabsf(s);
-            if (!(mag <= 3.402823466e38f) || (mag > 0.f && mag < 0x1p-90f)) {
+            if (!(fabsf(s) <= 3.402823466e38f) || (any_tiny && sh.tiny[h * G + gq])) {
                 const uint16_t* kr = (const uint16_t*)(kl + slot * upr) + (int64_t)(h0 + h) * D;
-                const uint16_t* qh = s_qp + (h * G + gq) * D;
-                s = 0.f;
-                for (int e = 0; e < D; ++e) {
-                    const float hi = __uint_as_float((uint32_t)qh[e] << 16);
-                    const float lo = __uint_as_float((uint32_t)qh[e + nqe] << 16) +
-                                     __uint_as_float((uint32_t)qh[e + 2 * nqe] << 16);
-                    const float qv = fabsf(hi) <= 3.402823466e38f ? hi + lo : hi;
-                    s = fmaf(qv, __uint_as_float((uint32_t)kr[e] << 16), s);
+                const uint16_t* qh = qr + (h * G + gq) * D;
+                double s64 = 0.0;
+                for (int j = 0; j < half; ++j) {
+                    const int e0 = interleaved ? 2 * j : j, e1 = interleaved ? 2 * j + 1 : j + half;
+                    const float2 y = rotate_pair(qh[e0], qh[e1], sh.cs[j], sh.sn[j]);
+                    s64 = fma((double)y.x, (double)__uint_as_float((uint32_t)kr[e0] << 16), s64);
+                    s64 = fma((double)y.y, (double)__uint_as_float((uint32_t)kr[e1] << 16), s64);
                 }
+                s = (float)s64;
             }
             out[(int64_t)(h * G + gq) * max_tokens + tok0 + i] = s;
         }

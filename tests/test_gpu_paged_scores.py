@@ -128,6 +128,49 @@ def test_paged_scores_non_finite_operands():
     assert torch.isfinite(sc[0, :4, 5:]).all()
 
 
+@pytest.mark.parametrize("scale", [1e-38, 1e-36, 1e-33, 1e-29])
+@pytest.mark.parametrize("interleaved", [False, True])
+def test_paged_scores_tiny_queries(scale, interleaved):
+    # a rotated query below 2^-110 does not fit three bf16 parts; keys that make
+    # its logits large, ordinary and small, and heads with a few tiny elements
+    bt, pk, q, m = _setup(2, 8, 2, 64, 60, 16, 3, seed=11)
+    pk[:, :, :, ::5] = (pk[:, :, :, ::5].float() * 1e30).to(torch.bfloat16)
+    pk[:, ::3] = (pk[:, ::3].float() * 1e-6).to(torch.bfloat16)
+    q[:, :6] = (q[:, :6].float() * scale).to(torch.bfloat16)
+    q[:, 6, 5:40] = (q[:, 6, 5:40].float() * scale).to(torch.bfloat16)
+    q[:, 7, 9] = 0
+    q[:, 5] = 0
+    sc, st = _run(bt, pk, q, m, 60, 16, 3, 1, interleaved)
+    assert st == 0
+    for r in range(2):
+        ref, mag, _ = _reference(bt, pk, q, m, 16, 3, 1, interleaved, r)
+        err = (sc[r, :, :int(m[r])].double() - ref).abs()
+        # (a rotated element below 2^-126 rounds to a multiple of 2^-149)
+        kmag = pk.double().abs().max()
+        assert (err <= 11 * 2.0 ** -24 * mag + 64 * 2.0 ** -149 * (1 + kmag)).all()
+
+
+def test_paged_scores_rotated_past_the_largest_bf16():
+    # an element between the largest bf16 and the largest fp32 after the rotation
+    bt, pk, q, m = _setup(1, 2, 1, 16, 4, 16, 0, seed=12)
+    q[:] = 0
+    q[0, :, 0], q[0, :, 8] = 2.8e38, 2.0e38
+    pk[:] = 0
+    pk[0, :, 0, 0], pk[0, :, 0, 8] = 1e-3, 1e-3
+    x0, x1 = float(q[0, 0, 0]), float(q[0, 0, 8])
+    rotated = {p: (x0 * np.cos(p) - x1 * np.sin(p), x1 * np.cos(p) + x0 * np.sin(p))
+               for p in range(1, 4000)}
+    best = next(p for p, y in rotated.items() if 3.398e38 < max(abs(y[0]), abs(y[1])) < 3.4026e38)
+    qp = torch.tensor([best], dtype=torch.int32, device="cuda")
+    sc = torch.zeros(1, 2, 4, device="cuda")
+    is_paged_scores(q, qp, pk, 0, bt, 16, 0, m, sc, nq=1, Hq=2, H=1, D=16, L=2,
+                    num_slots=pk.shape[1], max_blocks=bt.shape[1], max_tokens=4, rope_theta=THETA)
+    torch.cuda.synchronize()
+    e = sum(rotated[best]) * float(pk[0, 0, 0, 0])
+    got = sc[0, :, :int(m[0])].double()
+    assert torch.isfinite(got).all() and ((got - e).abs() <= 2.0 ** -20 * 4e35).all()
+
+
 @pytest.mark.parametrize("D", [16, 32, 64, 128, 256, 512])
 def test_paged_scores_precision(D):
     # against 64 bits no further off than fp32 multiply-adds over eight elements,
