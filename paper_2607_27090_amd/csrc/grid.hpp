@@ -1,4 +1,4 @@
-// Launch shapes: host arithmetic only.
+// Launch shapes: host arithmetic, and what the kernels share of it.
 #pragma once
 
 #include <stdint.h>
@@ -54,6 +54,55 @@ inline RowShares row_shares(int64_t rows, int tile, int step, int qtiles, int cu
         if (qtiles == 1) break;
     }
     return best;
+}
+
+// Paged logits: a launch has TokenRule::blocks blocks per request and head share
+// (`parts` of those), about `target` in all at full capacity, so that a large
+// max_tokens costs no blocks. The blocks of a request share out its m placed
+// tokens, in groups of 16: as many groups each as give `target` blocks if every
+// request placed m, or, with m close to the capacity, max_tokens. (With shares by capacity, 300 tokens of 131,072 were one
+// block's work: 32 requests of 32 heads of 32 140 us, by m 14.) The kernel is
+// small, and its first loads wait for its share: with divisions a call took 0.3
+// us longer, so the launch brings reciprocals.
+struct TokenRule {
+    uint32_t blocks;
+    uint32_t per_block;  // 2^32 / blocks, rounded up
+    uint32_t per_m;      // groups of a block for each of a request's, in 65536ths
+    uint32_t most;       // groups of a block at most
+    uint32_t half, full; // from `half` groups on, half of the capacity: `full` a block
+};
+struct TokenShare {
+    int32_t first, last;  // tokens [first, last)
+};
+
+constexpr int64_t token_groups(int64_t tokens) { return (tokens + 15) / 16; }
+
+// `most`: groups a block should have at most; kept while that takes no more than
+// four times `target` blocks (past it the empty ones of a short request cost
+// more than they give: the hardware starts one every few ns).
+inline TokenRule token_rule(int64_t max_tokens, int64_t parts, int target, uint32_t most) {
+    const int64_t groups = token_groups(max_tokens);
+    int64_t per = parts * groups / target > 1 ? parts * groups / target : 1;
+    if (per > most && (groups + most - 1) / most * parts <= 4 * (int64_t)target) per = most;
+    const int64_t blocks = (groups + per - 1) / per;
+    const int64_t per_m = blocks > 1 && parts < target ? parts * 65536 / target : 65536;
+    return {(uint32_t)blocks, blocks > 1 ? (uint32_t)((((uint64_t)1 << 32) + blocks - 1) / blocks) : 0,
+            (uint32_t)per_m, groups <= blocks * most ? most : UINT32_MAX,
+            (uint32_t)((groups + 1) / 2), (uint32_t)per};
+}
+
+constexpr TokenShare token_share(int32_t m, uint32_t block, const TokenRule& rule) {
+    const uint32_t groups = m > 0 ? ((uint32_t)m + 15) / 16 : 0;
+    // groups over blocks, rounded up (by one too many past 2^32 / blocks groups)
+    const uint32_t even = (uint32_t)(((uint64_t)(groups + rule.blocks - 1) * rule.per_block) >> 32);
+    uint32_t per = (uint32_t)(((uint64_t)groups * rule.per_m) >> 16);
+    per = per < even ? even : per;
+    per = per > rule.most ? rule.most : per;
+    per = groups >= rule.half ? rule.full : per;
+    const uint64_t first = (uint64_t)block * per;
+    if ((uint32_t)(first >> 32) != 0 || (uint32_t)first >= groups) return {0, 0};
+    const uint32_t f = (uint32_t)first;
+    return {(int32_t)(f * 16), f + per >= groups ? m : (int32_t)((f + per) * 16)};
 }
 
 }  // namespace is

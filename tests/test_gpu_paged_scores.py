@@ -85,6 +85,54 @@ def test_paged_scores_many_tokens_per_block():
         assert ((sc[r, :, :int(m[r])].double() - ref).abs() <= 11 * 2.0 ** -24 * mag).all()
 
 
+@pytest.mark.parametrize("nq,tokens,capacity", [
+    (200, 2700, 2700),              # past 512 tokens per block: mapped in two parts
+    (3, 50, 131_072), (3, 1, 5000), (70, 333, 9000),   # far below the capacity
+])
+def test_paged_scores_shares(nq, tokens, capacity):
+    P, start = 16, 7
+    bt, pk, q, m = _setup(nq, 6, 2, 32, tokens, P, start, seed=nq)
+    wide = torch.full((nq, -(-(start + capacity) // P)), -1, dtype=torch.int32, device="cuda")
+    wide[:, :bt.shape[1]] = bt
+    sc, st = _run(wide, pk, q, m, capacity, P, start, 1, False)
+    assert st == 0
+    for r in {0, 1, nq // 2, nq - 1}:
+        ref, mag, _ = _reference(bt, pk, q, m, P, start, 1, False, r)
+        n = int(m[r])
+        assert ((sc[r, :, :n].double() - ref).abs() <= 10 * 2.0 ** -24 * mag).all()
+        assert (sc[r, :, n:] == -7.0).all()
+
+
+def test_paged_scores_capacity_costs_nothing():
+    # 4 requests of up to 2,560 tokens in a buffer for them and in one for 131,072
+    # (10 and 209 us where a block's share followed the capacity)
+    bt, pk, q, m = _setup(4, 32, 32, 32, 2560, 16, 0, seed=5)
+    wide = torch.full((4, 131_072 // 16), -1, dtype=torch.int32, device="cuda")
+    wide[:, :bt.shape[1]] = bt
+
+    def us(bt, tokens):
+        sc = torch.empty(4, 32, tokens, device="cuda")
+
+        def call():
+            is_paged_scores(q, m, pk, 0, bt, 16, 0, m, sc, nq=4, Hq=32, H=32, D=32, L=2,
+                            num_slots=pk.shape[1], max_blocks=bt.shape[1], max_tokens=tokens,
+                            rope_theta=THETA)
+
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        return best
+
+    tight, loose = us(bt, 2560), us(wide, 131_072)
+    assert loose < 3 * tight, (tight, loose)
+
+
 def test_paged_scores_skips_bad_tokens_only():
     bt, pk, q, m = _setup(2, 8, 2, 128, 100, 16, 3, seed=4)
     bt[0, 2] = -1

@@ -20,6 +20,14 @@ extern "C" int64_t shares(int64_t rows, int qtiles, int cus, int* blocks) {
     *blocks = g.blocks;
     return g.rows;
 }
+extern "C" void token_rule(int64_t max_tokens, int64_t parts, int target, is::TokenRule* r) {
+    *r = is::token_rule(max_tokens, parts, target, 32);
+}
+extern "C" void token_share(int m, unsigned block, const is::TokenRule* r, int* fl) {
+    const is::TokenShare s = is::token_share(m, block, *r);
+    fl[0] = s.first;
+    fl[1] = s.last;
+}
 """
 
 
@@ -74,3 +82,33 @@ def test_row_shares_keep_the_cus_busy(lib, rows):
         walk = -(-blocks * qtiles // cus) * -(-share // 256)
         even = tiles * qtiles / cus
         assert walk <= 1.34 * even + 1, (qtiles, blocks, share, walk, even)
+
+
+@pytest.mark.parametrize("capacity", [1, 16, 17, 300, 640, 2560, 16_500, 131_072, 2 ** 31 - 1])
+@pytest.mark.parametrize("parts", [1, 2, 4, 64, 845, 1000, 65_535])
+def test_token_shares_follow_what_is_placed(lib, capacity, parts):
+    target, i64 = 1024, ctypes.c_int64
+    rule = (ctypes.c_uint32 * 6)()
+    lib.token_rule(i64(capacity), i64(parts), target, rule)
+    blocks, most = rule[0], rule[3]
+    # no more than four times `target` blocks, or one per part
+    assert 1 <= blocks <= -(-capacity // 16) and blocks * parts <= max(4 * target, parts)
+    # 512 tokens a block where the blocks hold the capacity in such shares
+    assert most == (32 if blocks * 512 >= capacity else 2 ** 32 - 1)
+    for m in {0, 1, 15, 16, 17, 33, 300, 2500, capacity // 2, capacity}:
+        if m > capacity or blocks > 5000:
+            continue
+        at, longest = 0, 0
+        fl = (ctypes.c_int * 2)()
+        for b in range(blocks):
+            lib.token_share(m, b, rule, fl)
+            if fl[0] < fl[1]:
+                assert fl[0] == at and fl[0] % 16 == 0
+                at, longest = fl[1], max(longest, fl[1] - fl[0])
+        assert at == max(m, 0) and longest <= 16 * most
+        # every CU's share of what is placed, whatever the capacity
+        groups = -(-m // 16)
+        if m < capacity // 2:
+            assert longest <= 16 * max(1, -(-groups // blocks), parts * groups // target) + 16 * (m > 2 ** 25)
+        else:
+            assert longest <= 16 * max(1, parts * -(-capacity // 16) // target)
