@@ -65,20 +65,34 @@ struct FusedLayout {
     int64_t sample;
 };
 
-// The sample: one to four select chunks, at most a quarter of the bank. Its
-// dense scan takes one row tile per block whatever its size up to a row tile
-// per CU, and a larger sample leaves fewer rows to the filtered scan and a
-// tighter bound (the 1M-row bank: 65,536 rows).
-int64_t fused_sample(int64_t n) {
+// The sample whose workspace a call asks for: one to four select chunks, at
+// most a quarter of the bank.
+int64_t fused_sample_max(int64_t n) {
     const int64_t chunk = is::select_chunk_len();
     const int64_t c = std::min<int64_t>(4, std::max<int64_t>(1, n / (4 * chunk)));
     return c * chunk;
 }
 
-FusedLayout fused_layout(int64_t n, int32_t k, int32_t nq) {
+// The sample a call takes when its workspace allows (a smaller one leaves more
+// survivor room to provide for; the result is the same with any): as few rows
+// as leave about 2,048 survivors per query, expected k (n - S) / S, in steps of
+// 4,096 and no fewer than 4 k, or one row tile for every CU, which takes no
+// longer to scan than fewer and gives a tighter bound. Rows past both are scores
+// to write and to rank. The most / the chosen / the fewest rows, us per
+// retrieval: 1,024 queries over 50,000 rows of 768 160 / 158 / 172; 256 over 1M
+// of 1,024 631 / 618 / 640; 8,000 over 50,000 of 256 642 / 458 / 493; 33,000 over
+// 33,000 of 64 1,812 / 1,018 / 1,044.
+int64_t fused_sample(int64_t n, int32_t k, int32_t nq) {
+    const int64_t rows = std::max<int64_t>((int64_t)k * n / 2048, 4 * (int64_t)k);
+    const int64_t step = 4096;
+    const int64_t few = std::max<int64_t>(1, (rows + step - 1) / step) * step;
+    const int64_t round = is::mfma_round_rows(nq) / step * step;
+    return std::min(fused_sample_max(n), std::max(few, round));
+}
+
+FusedLayout fused_layout(int64_t n, int32_t k, int32_t nq, int64_t S) {
     FusedLayout lay{};
-    const int64_t S = fused_sample(n);
-    const int64_t nch = S / is::select_chunk_len();
+    const int64_t nch = (S + is::select_chunk_len() - 1) / is::select_chunk_len();
     const int64_t gmax = is::mfma_max_blocks();
     lay.sample = S;
     size_t off = 0;
@@ -143,7 +157,8 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
         // Sample and rest are scored by one kernel: equal rows on either side
         // of S then have equal scores, and the bound is a score of the kind it
         // is compared with.
-        const FusedLayout fl = fused_layout(n, k, nq);
+        FusedLayout fl = fused_layout(n, k, nq, fused_sample(n, k, nq));
+        if (fl.total > ws_bytes) fl = fused_layout(n, k, nq, fused_sample_max(n));
         const int64_t S = fl.sample;
         float* sc = (float*)(ws + fl.scores_off);
         uint64_t* first = (uint64_t*)(ws + fl.first_off);
@@ -155,7 +170,7 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
         uint32_t* tmax = tiles ? (uint32_t*)regions : nullptr;
         e = is::launch_scan_mfma(query_emb, bank, d, nq, 0, S, sc, S, tmax, st);
         if (e != hipSuccess) return fail(IS_ERR_HIP, "scan launch: %s", hipGetErrorString(e));
-        const int nch = (int)(S / is::select_chunk_len());
+        const int nch = (int)((S + is::select_chunk_len() - 1) / is::select_chunk_len());
         if (tiles) {
             e = is::launch_select_tiles(sc, tmax, S, rows, k, nq, nullptr, nullptr, first, st);
         } else if (nch == 1) {
@@ -231,7 +246,7 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
 size_t retrieve_need(int64_t n, int32_t d, int32_t k, int32_t nq, int64_t bank_stride,
                      int32_t dtype) {
     return fused_applies(n, d, nq, bank_stride, dtype)
-               ? fused_layout(n, k, nq).total
+               ? fused_layout(n, k, nq, fused_sample_max(n)).total
                : retrieve_layout(n, k, nq).total;
 }
 
@@ -241,7 +256,8 @@ size_t retrieve_want(int64_t n, int32_t d, int32_t k, int32_t nq, int32_t dtype,
     size_t total = std::max(retrieve_layout(n, k, nq).total,
                             dense_tiles_bytes(n, d, k, nq, 0, dtype, plan));
     if (fused_applies(n, d, nq, 0, dtype))
-        total = std::max(total, fused_layout(n, k, nq).total);
+        total = std::max({total, fused_layout(n, k, nq, fused_sample_max(n)).total,
+                          fused_layout(n, k, nq, fused_sample(n, k, nq)).total});
     return total;
 }
 

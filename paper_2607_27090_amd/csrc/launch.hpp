@@ -21,6 +21,8 @@ bool scan_mfma_applies(int64_t n, int d, int nq, int64_t bank_stride, int dtype)
 // mfma_max_blocks() blocks; rows_per_block is a multiple of 32).
 void mfma_grid(int64_t rows, int nq, int* blocks, int64_t* rows_per_block);
 int mfma_max_blocks();
+// Rows that one round of blocks over all query tiles scores, a row tile each.
+int64_t mfma_round_rows(int nq);
 int mfma_tile_rows();
 // Dense scores of rows [row_begin, row_end): scores[q * ld + row - row_begin];
 // with tmax also the largest score of every mfma_tile_rows() rows, as order

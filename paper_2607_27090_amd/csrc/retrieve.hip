@@ -25,6 +25,8 @@
 //     bounds those); the survivors of the filtered matrix-core scan are
 //     ranked by select_regions_kernel. Ties go to the lower id (score desc,
 //     id asc).
+#include <algorithm>
+
 #include "grid.hpp"
 #include "launch.hpp"
 #include "wave.hpp"
@@ -604,6 +606,11 @@ void mfma_grid(int64_t rows, int nq, int* blocks, int64_t* rows_per_block) {
     const RowShares g = row_shares(rows, kMmRows, 32, (nq + kMmQ - 1) / kMmQ, cus);
     *blocks = g.blocks;
     *rows_per_block = g.rows;
+}
+
+int64_t mfma_round_rows(int nq) {
+    const int nqt = (nq + kMmQ - 1) / kMmQ;
+    return (int64_t)std::max(1, compute_units() / nqt) * kMmRows;
 }
 
 int mfma_max_blocks() { return kMmMaxBlocks; }
@@ -1420,8 +1427,15 @@ constexpr int kSelManyQueries = 512;
 hipError_t launch_select_scores(const float* scores, int64_t n, int k, int nq, int nchunks,
                                 uint64_t* cand, hipStream_t st) {
     dim3 grid((unsigned)nchunks, (unsigned)nq);
-    hipLaunchKernelGGL((select_small_kernel<kSelKpt>), grid, dim3(kSelThreads), 0, st, scores, n, k,
-                       (int32_t*)nullptr, (float*)nullptr, cand, nchunks);
+    if (n <= 4 * kSelThreads && k <= 256 && nq >= kSelManyQueries)
+        hipLaunchKernelGGL((select_small_kernel<16, 256>), grid, dim3(256), 0, st, scores, n, k,
+                           (int32_t*)nullptr, (float*)nullptr, cand, nchunks);
+    else if (n <= 4 * kSelThreads)
+        hipLaunchKernelGGL((select_small_kernel<4>), grid, dim3(kSelThreads), 0, st, scores, n, k,
+                           (int32_t*)nullptr, (float*)nullptr, cand, nchunks);
+    else
+        hipLaunchKernelGGL((select_small_kernel<kSelKpt>), grid, dim3(kSelThreads), 0, st, scores,
+                           n, k, (int32_t*)nullptr, (float*)nullptr, cand, nchunks);
     return hipGetLastError();
 }
 
