@@ -145,7 +145,8 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
     const RetrieveLayout lay = retrieve_layout(n, k, nq);
     const bool direct = is::scan_direct_applies(n, d, plan, bank_stride, dtype);
     const bool mfma = !direct && is::scan_mfma_applies(n, d, plan, bank_stride, dtype);
-    const bool fused = mfma && fused_applies(n, d, nq, bank_stride, dtype);
+    const bool fused = mfma && fused_applies(n, d, nq, bank_stride, dtype) &&
+                       !is::mfma_few_rounds(n, nq);
     char* ws = (char*)workspace;
     hipError_t e;
     if (fused) {
@@ -237,10 +238,10 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
     return ok();
 }
 
-// Workspace a call asks for. A call that the direct scan takes away from the
-// filtered path needs less than this; what it asks for stays, so the sizes
-// that a given workspace or the fixed scratch serves do not depend on which
-// scan is the faster one. (With a little more than it asks for, up to what
+// Workspace a call asks for. A call that the direct or the dense scan takes away
+// from the filtered path needs less than this; what it asks for stays, so the
+// sizes that a given workspace or the fixed scratch serves do not depend on
+// which is the faster one. (With a little more than it asks for, up to what
 // is_retrieve_workspace_size says, the faster one of two paths with the same
 // results is taken.)
 size_t retrieve_need(int64_t n, int32_t d, int32_t k, int32_t nq, int64_t bank_stride,

@@ -23,6 +23,8 @@ void mfma_grid(int64_t rows, int nq, int* blocks, int64_t* rows_per_block);
 int mfma_max_blocks();
 // Rows that one round of blocks over all query tiles scores, a row tile each.
 int64_t mfma_round_rows(int nq);
+// So few row tiles that the dense scan is faster than the filtered one.
+bool mfma_few_rounds(int64_t n, int nq);
 int mfma_tile_rows();
 // Dense scores of rows [row_begin, row_end): scores[q * ld + row - row_begin];
 // with tmax also the largest score of every mfma_tile_rows() rows, as order

@@ -613,6 +613,15 @@ int64_t mfma_round_rows(int nq) {
     return (int64_t)std::max(1, compute_units() / nqt) * kMmRows;
 }
 
+// At most two rounds of row tiles over all CUs: the filter's sample is a round of
+// its own, and with so few every score is stored in less time. us per retrieval
+// (d = 768 / 1,536) filtered and dense: 256 queries over 65,000 rows 83 / 125 and
+// 60 / 87, over 110,000 113 / 179 and 95 / 142; 64 over 125,000 86 / 140 and 74 /
+// 112; but three rounds, 256 over 190,000, 140 / 228 and 151 / 222.
+bool mfma_few_rounds(int64_t n, int nq) {
+    return (n + kMmRows - 1) / kMmRows * ((nq + kMmQ - 1) / kMmQ) <= 2 * (int64_t)compute_units();
+}
+
 int mfma_max_blocks() { return kMmMaxBlocks; }
 
 int mfma_tile_rows() { return kMmTileRows; }

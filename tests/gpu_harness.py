@@ -19,6 +19,19 @@ def log(msg: str) -> None:
     sys.stdout.flush()
 
 
+def filtered(n: int, nq: int) -> bool:
+    """A bf16 retrieval of nq >= 32 queries (d >= 64) on one bank goes through
+    the filtered scan: past the direct scan's product and past two rounds of 256
+    x 256 tiles over the CUs (and past two select chunks of rows)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return n > 32768 and n * nq > 6_000_000 and -(-n // 256) * -(-nq // 256) > 2 * cus
+
+
+def sample_most(n: int) -> int:
+    """The largest row sample of the filtered scan: one to four select chunks."""
+    return 16384 * min(4, max(1, n // 65536))
+
+
 def u16(t: torch.Tensor) -> np.ndarray:
     return t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
 

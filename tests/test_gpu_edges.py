@@ -14,7 +14,7 @@ from paper_2607_27090_amd import (IS_DEV_BAD_BLOCK, IS_DEV_BT_SHORT, IS_DEV_CAPA
                                   is_inject, is_slot_map)
 from paper_2607_27090_amd.pipeline import RequestBuffers
 from tests import parity
-from tests.gpu_harness import Instance, host_emb, log, u16
+from tests.gpu_harness import Instance, filtered, host_emb, log, sample_most, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -153,7 +153,9 @@ def test_retrieve_filtered_scan_every_row_survives():
     # k-th best. Every survivor region fills to capacity and the final ranking
     # runs over several chunks; exact ties go to the lower ids.
     g = torch.Generator(device="cuda").manual_seed(91)
-    n, d, k, nq, S = 100_000, 64, 50, 32, 16384
+    n, d, k, nq = 140_000, 64, 50, 64
+    S = sample_most(n)
+    assert filtered(n, nq)
     bank = torch.randn(n, d, generator=g, device="cuda")
     bank = (bank / bank.norm(dim=1, keepdim=True)).to(torch.bfloat16)
     v = bank[7].clone()
@@ -168,11 +170,12 @@ def test_retrieve_filtered_scan_every_row_survives():
 
 def test_retrieve_filtered_scan_four_chunk_sample():
     # a bank of 300,000 rows takes a sample of four select chunks (65,536
-    # rows), whose chunk winners are merged by rank into the bound; the
-    # rows after the sample all equal query 0, so for it every one of them
-    # survives the filter, and its ties go to the lower ids
+    # rows), ranked into the bound; the rows after the sample all equal query
+    # 0, so for it every one of them survives the filter, and its ties go to
+    # the lower ids
     g = torch.Generator(device="cuda").manual_seed(93)
     n, d, k, nq, S = 300_000, 64, 50, 32, 4 * 16384
+    assert filtered(n, nq) and S == sample_most(n)
     bank = torch.randn(n, d, generator=g, device="cuda")
     bank = (bank / bank.norm(dim=1, keepdim=True)).to(torch.bfloat16)
     v = bank[7].clone()
@@ -189,7 +192,8 @@ def test_retrieve_filtered_scan_negative_scores():
     # every score is negative, so the sample threshold is below the zero
     # scores of the padding rows of partial tiles: they must not be ranked
     g = torch.Generator(device="cuda").manual_seed(92)
-    n, d, k, nq = 40_000, 128, 20, 40
+    n, d, k, nq = 140_033, 128, 20, 64
+    assert filtered(n, nq)
     bank = torch.rand(n, d, generator=g, device="cuda") + 0.01
     bank = (bank / bank.norm(dim=1, keepdim=True)).to(torch.bfloat16)
     q = -(torch.rand(nq, d, generator=g, device="cuda") + 0.01)

@@ -8,7 +8,7 @@ import torch
 
 import workloads
 from paper_2607_27090_amd.pipeline import RequestBuffers, run_request
-from tests.gpu_harness import log
+from tests.gpu_harness import filtered, log
 
 pytestmark = pytest.mark.gpu
 
@@ -68,7 +68,8 @@ def test_request_graph_replays_match_eager(fused):
 
 
 def test_filtered_retrieval_graph_replays_match_eager():
-    w = workloads.TINY.with_(n=60000, d_e=256, k=40, nq=64, emb_dtype="bf16", index=52)
+    w = workloads.TINY.with_(n=140000, d_e=256, k=40, nq=64, emb_dtype="bf16", index=52)
+    assert filtered(w.n, w.nq)
     bank = workloads.make_bank(w, "cuda")
     q_in = workloads.make_queries(w, "cuda", variant=0).clone()
     gbuf = RequestBuffers(n=w.n, d=w.d_e, k=w.k, nq=w.nq, emb_dtype=bank.dtype, max_tokens=1)

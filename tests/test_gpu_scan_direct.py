@@ -14,7 +14,7 @@ from paper_2607_27090_amd import (InferScaleError, is_ann_build, is_ann_build_wo
                                   is_retrieve, is_retrieve_workspace_size)
 from paper_2607_27090_amd.pipeline import RequestBuffers
 from tests import parity
-from tests.gpu_harness import host_emb, log
+from tests.gpu_harness import filtered, host_emb, log, sample_most
 
 pytestmark = pytest.mark.gpu
 
@@ -207,14 +207,14 @@ def test_ranking_does_not_walk_whole_rows():
     assert times["600 results"] < 4 * plain and times["1,024 results"] < 8 * plain
 
 
-@pytest.mark.parametrize("n,S", [(60_000, 16384), (140_000, 32768)])
-def test_filtered_scan_every_row_survives_many_queries(n, S):
-    # a product past the direct scan's bound: row sample (ranked in one or two
-    # select chunks), then the filter; the rows after the sample all equal
-    # query 0, so its survivor regions fill to capacity and its ties go to the
-    # lower ids
+@pytest.mark.parametrize("n,nq", [(70_000, 300), (140_000, 200)])
+def test_filtered_scan_every_row_survives_many_queries(n, nq):
+    # row sample (of one or two select chunks), then the filter; the rows after
+    # the sample all equal query 0, so its survivor regions fill to capacity and
+    # its ties go to the lower ids
     g = torch.Generator(device="cuda").manual_seed(n)
-    d, k, nq = 72, 50, 200
+    d, k, S = 72, 50, sample_most(n)
+    assert filtered(n, nq)
     bank, q = _unit(n, d, g).to(torch.bfloat16), _unit(nq, d, g).to(torch.bfloat16)
     v = bank[7].clone()
     bank[S:] = v
@@ -238,9 +238,9 @@ def _asked(call):
 @pytest.mark.parametrize("n,d,nq,k,dt", [
     (20_000, 72, 40, 30, torch.float32),       # chunk winners instead of tile maxima
     (30_000, 72, 300, 50, torch.bfloat16),     # the same after the block-staged scan
-    (40_000, 72, 600, 65, torch.bfloat16),     # filtered: the larger row sample; small ranking blocks
-    (90_000, 72, 100, 700, torch.bfloat16),    # filtered, a sample of several chunks' maxima
-    (400_000, 72, 40, 100, torch.bfloat16),    # filtered, 20,480 against 65,536 rows
+    (40_000, 72, 2000, 20, torch.bfloat16),    # filtered: the larger row sample; small ranking blocks
+    (140_000, 72, 100, 700, torch.bfloat16),   # filtered, a sample ranked by its chunks' winners
+    (400_000, 72, 40, 100, torch.bfloat16),    # filtered
 ])
 def test_smaller_workspaces_give_the_same(n, d, nq, k, dt):
     # small-integer operands: exact scores with many ties, so any path must rank
@@ -266,7 +266,7 @@ def test_smaller_workspaces_give_the_same(n, d, nq, k, dt):
         assert torch.equal(sc.double(), o.values[:, :k])
 
 
-@pytest.mark.parametrize("n,d,nq", [(60_000, 768, 200), (100_000, 1024, 100), (400_000, 768, 40)])
+@pytest.mark.parametrize("n,d,nq", [(70_000, 768, 300), (140_000, 1024, 100), (400_000, 768, 40)])
 def test_filtered_scan_scores_equal_rows_equally(n, d, nq):
     # each of 40 queries is a row of the sample that also stands among the rows
     # after it: both copies score the same bits and the lower id comes first,
@@ -276,6 +276,7 @@ def test_filtered_scan_scores_equal_rows_equally(n, d, nq):
     first = torch.arange(40, device="cuda")
     bank[n - 50 + first] = bank[first]
     q[:40] = bank[first]
+    assert filtered(n, nq)
     for k in (50, 1):
         ids = torch.empty(nq, k, dtype=torch.int32, device="cuda")
         sc = torch.empty(nq, k, device="cuda")
