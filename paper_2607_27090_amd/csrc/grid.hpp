@@ -105,4 +105,26 @@ constexpr TokenShare token_share(int32_t m, uint32_t block, const TokenRule& rul
     return {(int32_t)(f * 16), f + per >= groups ? m : (int32_t)((f + per) * 16)};
 }
 
+// Workgroups per CU of an injection. The tokens a request places differ (ten
+// facts of 16 to 64 tokens: 280 to 510), so with many requests equal shares of
+// the CUs end far apart: from 8 requests on, a request's share is cut into
+// several workgroups that the hardware hands out as CUs come free. One more per
+// CU costs 4 to 5 us whatever it finds to do (the hardware starts a workgroup
+// of 12 waves every 20 ns), so there is one for each 4 MiB of a CU's expected
+// bytes. What will be placed is not known here: max_tokens is a buffer's size
+// (8 requests of 50 tokens in buffers for 32,768 took 94 us instead of 25 with
+// workgroups by max_tokens) and facts are a few dozen tokens, so 32 per fact are
+// expected. Workgroups per CU 1 / 2 / 4 / 8 / 16, us: 64 requests of 10 facts of
+// 16 to 64 tokens 1,518 / 1,452 / 1,417 / 1,418 / 1,389, of 3 facts 454 / 413 /
+// 395 / 393 / 402; 16 of 20 facts 649 / 654 / 655 / 659 / 672; 64 of 10 facts of
+// 4 to 12 tokens 269 / 270 / 271 / 277 / 294, of one or two tokens 57 / 61 / 69 /
+// 81 / 117; but 4 requests of 50 facts 413 / 426 / - / 445 / 491.
+inline int inject_pieces(int nq, int k, int max_tokens, int64_t row_elements, int cus) {
+    if (nq < 8) return 1;
+    const int64_t expected = (int64_t)k * 32 < max_tokens ? (int64_t)k * 32 : max_tokens;
+    const double bytes = 8.0 * nq * (double)expected * (double)row_elements;  // K and V, in and out
+    const double pieces = 1.0 + bytes / ((double)(4 << 20) * cus);
+    return pieces < 4.0 ? (int)pieces : 4;
+}
+
 }  // namespace is

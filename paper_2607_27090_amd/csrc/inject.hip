@@ -43,6 +43,7 @@
 #include <atomic>
 
 #include "common.hpp"
+#include "grid.hpp"
 #include "launch.hpp"
 
 namespace is {
@@ -56,9 +57,6 @@ constexpr int kInjLayers = 1;      // layers of one work item (2 and 4 measured 
 // block-table entries each thread loads with the fact ids (PLACE); blocks
 // beyond 2 * 1024 are read after the scan
 constexpr int kInjBtAhead = 2;
-
-constexpr int64_t kInjShareBytes = 4 << 20;  // a workgroup's share of several (launch_inject)
-constexpr int kInjMaxPieces = 16;
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -450,24 +448,11 @@ hipError_t launch_inject(const int32_t* ids, const void* preK, const void* V, co
     // with nothing to place the plain inject has no work; the fused launch
     // still runs to validate the requests and write m
     if (items_max == 0 && !place) return hipSuccess;
-    // one workgroup per CU, shared by the requests; the shape depends on
-    // max_tokens only, never on m. The tokens a request places differ (ten
-    // facts of 16 to 64 tokens: 280 to 510), so with many requests equal shares
-    // of the CUs end far apart: from 8 requests on, a request's share is cut
-    // into several workgroups that the hardware hands out as CUs come free,
-    // each of at least kInjShareBytes at full capacity (a workgroup's set-up
-    // costs 5 us). Pieces of each share, us per request batch: 64 requests of
-    // 10 facts 1 / 8 / 16 / 32: 1,534 / 1,422 / 1,408 / 1,419; 64 of 30 facts
-    // 3,957 / 3,727 / 3,687 / 3,689; 8 of 20 facts, 80 layers: 1,196 / 1,143 /
-    // 1,154 / 1,175; but 4 of 50 facts 413 / 426 / 445 / 491.
+    // one workgroup per CU, shared by the requests, or several
+    // (inject_pieces); the shape depends on the arguments only, never on m
     const int cus = compute_units();
-    int64_t pieces = 1;
-    if (nq >= 8) {
-        const double bytes = 8.0 * nq * max_tokens * L * H * D;
-        pieces = (int64_t)(bytes / ((double)kInjShareBytes * cus));
-        pieces = pieces < 1 ? 1 : (pieces > kInjMaxPieces ? kInjMaxPieces : pieces);
-    }
-    int64_t per_req = cus * pieces / nq;
+    int64_t per_req =
+        cus * (int64_t)inject_pieces(nq, k, max_tokens, (int64_t)L * H * D, cus) / nq;
     if (per_req > items_max) per_req = items_max;
     if (per_req < 1) per_req = 1;
     dim3 grid((unsigned)per_req, (unsigned)nq);

@@ -28,6 +28,9 @@ extern "C" void token_share(int m, unsigned block, const is::TokenRule* r, int* 
     fl[0] = s.first;
     fl[1] = s.last;
 }
+extern "C" int pieces(int nq, int k, int max_tokens, int64_t row_elements, int cus) {
+    return is::inject_pieces(nq, k, max_tokens, row_elements, cus);
+}
 """
 
 
@@ -112,3 +115,13 @@ def test_token_shares_follow_what_is_placed(lib, capacity, parts):
             assert longest <= 16 * max(1, -(-groups // blocks), parts * groups // target) + 16 * (m > 2 ** 25)
         else:
             assert longest <= 16 * max(1, parts * -(-capacity // 16) // target)
+
+
+@pytest.mark.parametrize("nq,k,row_elements,want", [
+    (1, 50, 32 * 1024, 1), (7, 100, 80 * 1024, 1), (8, 3, 32 * 1024, 1), (64, 10, 32 * 1024, 4),
+    (64, 3, 32 * 1024, 2), (65_535, 1024, 80 * 1024, 4)])
+def test_injection_workgroups_do_not_follow_the_capacity(lib, nq, k, row_elements, want):
+    # a buffer for longer requests than are placed costs no workgroups
+    for capacity in (64 * k, 8192 + 64 * k, 2 ** 31 - 1):
+        assert lib.pieces(nq, k, capacity, ctypes.c_int64(row_elements), 256) == want
+    assert lib.pieces(nq, k, 0, ctypes.c_int64(row_elements), 256) == 1
