@@ -58,6 +58,17 @@ __device__ __forceinline__ float key_score(uint64_t key) {
     return score_from_order_bits((uint32_t)(key >> 32));
 }
 
+// ---- wave synchronisation ----------------------------------------------------
+
+// Between LDS writes and reads (or reads and writes) of different lanes of one
+// wave: LDS operations of a wave complete in order, so this is no instruction,
+// but the compiler must not move either across it.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // ---- wave reductions ---------------------------------------------------------
 
 __device__ __forceinline__ float wave_sum(float v) {

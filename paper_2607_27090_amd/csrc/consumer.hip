@@ -234,6 +234,7 @@ __global__ __launch_bounds__(kConsThreads) void paged_scores_kernel(
                 if (c + 1 < nch) load(item, c + 1, kv);
                 else load(item + kConsWaves, 0, kv);
                 __builtin_amdgcn_sched_barrier(0);
+                wave_lds_sync();
                 if (have != h * nch + c) {
                     have = h * nch + c;
 #pragma unroll
@@ -258,6 +259,7 @@ __global__ __launch_bounds__(kConsThreads) void paged_scores_kernel(
                             __builtin_bit_cast(bf16x8_c, fa[rt][ks]), __builtin_bit_cast(bf16x8_c, fb),
                             acc[rt], 0, 0, 0);
                 }
+                wave_lds_sync();
             }
             // lane: query head 4 rt + lane / 16, token lane % 16, its three parts
             const int i = g * 16 + col;
