@@ -9,11 +9,14 @@
 // which the three launches and two pointer queries are 10.
 //
 // Anything out of the ordinary (a failed check, a host-resident store, an
-// argument of another type) makes a function return None with nothing called;
-// the caller then takes the Python path, which handles it or raises.
+// argument of another type, a tensor whose size or pointer torch will not give)
+// makes a function return None with nothing called; the caller then takes the
+// Python path, which handles it or raises.
 #include <Python.h>
 
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <exception>
 
 #include "inferscale.h"
 
@@ -364,7 +367,19 @@ PyObject* bind(PyObject*, PyObject* args) {
     Py_RETURN_NONE;
 }
 
-#define IS_FAST(NAME) {#NAME, (PyCFunction)(void (*)(void))NAME, METH_FASTCALL, nullptr}
+// torch's accessors throw (a tensor without memory of its own, symbolic sizes),
+// and no C++ exception may pass through the interpreter. All of them come before
+// the entry point is called.
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* v, Py_ssize_t n) {
+    try {
+        return F(self, v, n);
+    } catch (const std::exception&) {
+        Py_RETURN_NONE;
+    }
+}
+
+#define IS_FAST(NAME) {#NAME, (PyCFunction)(void (*)(void))guarded<NAME>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {{"bind", bind, METH_VARARGS, nullptr},
                          IS_FAST(retrieve),
                          IS_FAST(slot_map),

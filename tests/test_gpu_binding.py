@@ -66,6 +66,23 @@ def test_native_path_leaves_refusals_to_the_python_path():
         isl.is_retrieve(*a, nq=2, workspace=kw["workspace"][:256])
 
 
+def test_tensors_without_memory_of_their_own_raise():
+    # torch may refuse a tensor's pointer by a C++ exception: it must come out as a
+    # Python one
+    a, kw = _args()
+    want = _ids(a, kw)
+    for i in (0, 1, 5):
+        b = list(a)
+        b[i] = torch._to_functional_tensor(a[i])
+        with pytest.raises(RuntimeError):
+            isl.is_retrieve(*b, **kw)
+        b[i] = a[i].clone()
+        torch._C._set_throw_on_mutable_data_ptr(b[i])
+        with pytest.raises(RuntimeError):
+            isl.is_retrieve(*b, **kw)
+    np.testing.assert_array_equal(_ids(a, kw), want)
+
+
 def test_status_may_be_unsigned_and_scores_absent():
     from tests.gpu_harness import Instance
     import workloads
