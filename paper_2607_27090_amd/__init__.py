@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch  # loaded first so the library binds to torch's HIP runtime
 
@@ -58,10 +59,12 @@ class InferScaleError(RuntimeError):
 
 
 _lib = None
-# The native marshalling module once the library is loaded. Its functions check
-# a call's arguments and make the call, returning its code, or return None with
-# nothing called when an argument is not an ordinary one; the Python path below
-# them then handles it or raises.
+# The native marshalling module once the library is loaded, if it is built (it
+# needs a C++ compiler and the headers of Python and torch; the library does
+# not, and every call works without it). Its functions check a call's arguments
+# and make the call, returning its code, or return None with nothing called when
+# an argument is not an ordinary one; the Python path below them then handles it
+# or raises.
 _native = None
 
 
@@ -111,12 +114,17 @@ def load_library() -> ctypes.CDLL:
     lib.is_ann_search.argtypes = [P, i32, P, i64, i32, i32, P, i32, P, P, i32, i32, i32, i32,
                                   i32, P, P, P, P, P, P, sz, P]
     lib.is_ann_search.restype = ctypes.c_int
-    from . import _binding
-    _binding.bind(_resolve_stream, {
-        f: ctypes.cast(getattr(lib, f), ctypes.c_void_p).value
-        for f in ("is_retrieve", "is_slot_map", "is_inject_rotary", "is_place_inject",
-                  "is_paged_scores", "is_ann_search")})
-    _native = _binding
+    try:
+        from . import _binding
+    except ImportError as e:
+        warnings.warn(f"native argument marshalling is not built ({e}): every call takes about "
+                      "10 us more on the host", RuntimeWarning, stacklevel=2)
+    else:
+        _binding.bind(_resolve_stream, {
+            f: ctypes.cast(getattr(lib, f), ctypes.c_void_p).value
+            for f in ("is_retrieve", "is_slot_map", "is_inject_rotary", "is_place_inject",
+                      "is_paged_scores", "is_ann_search")})
+        _native = _binding
     _lib = lib
     return lib
 

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import concurrent.futures
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -37,11 +38,17 @@ def _compile(src: str) -> str:
 
 
 def _compile_binding() -> None:
-    """The Python binding's marshalling module (host code only)."""
+    """The Python binding's marshalling module (host code only). Where there is
+    no host compiler or no Python header the package works without it."""
     import torch
     from torch.utils import cpp_extension
+    cxx = os.environ.get("CXX", "g++")
+    python_h = os.path.join(sysconfig.get_paths()["include"], "Python.h")
+    if shutil.which(cxx) is None or not os.path.exists(python_h):
+        print(f"not built: {BINDING} (needs {cxx} and {python_h})", file=sys.stderr)
+        return
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-fPIC", "-std=c++17", "-shared",
+    cmd = [cxx, "-O2", "-fPIC", "-std=c++17", "-shared",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE,
            "-I", sysconfig.get_paths()["include"],
            *[a for d in cpp_extension.include_paths() for a in ("-isystem", d)],

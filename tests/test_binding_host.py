@@ -4,10 +4,16 @@ count the call's shape arguments imply, before any pointer reaches the
 library (a wrong dtype or a short buffer would otherwise be read or written
 past its end on the device). Host tensors are used: a correctly typed and
 sized argument list gets past every check and stops at the device check."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
 import paper_2607_27090_amd as isl
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 i32, i64, f32, bf16, f64 = torch.int32, torch.int64, torch.float32, torch.bfloat16, torch.float64
 
@@ -27,6 +33,34 @@ def call_retrieve(a):
     a = dict(a)
     isl.is_retrieve(a.pop("query_emb"), a.pop("bank"), a.pop("n"), a.pop("d"), a.pop("k"),
                     a.pop("out_ids"), a.pop("out_scores"), **a)
+
+
+@pytest.mark.parametrize("hidden", ["paper_2607_27090_amd._binding", None])
+def test_package_loads_without_the_native_marshalling(hidden):
+    # the HIP library alone is enough: the calls' Python path is complete
+    code = ("import sys, warnings\n"
+            f"if {hidden!r}: sys.modules[{hidden!r}] = None\n"
+            "import torch, paper_2607_27090_amd as isl\n"
+            "with warnings.catch_warnings(record=True) as w:\n"
+            "    warnings.simplefilter('always')\n"
+            "    isl.load_library()\n"
+            "print(isl.is_version(), isl._native is None, len(w))\n"
+            "t = torch.zeros(4, 8)\n"
+            "try: isl.is_retrieve(t, t, 4, 8, 1, torch.zeros(1, 1, dtype=torch.int32),\n"
+            "                     workspace=torch.zeros(256, dtype=torch.uint8))\n"
+            "except ValueError as e: print('refused')\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert r.returncode == 0, r.stderr
+    assert "inferscale-gfx950" in r.stdout and "refused" in r.stdout
+    assert (f"{hidden is not None} {int(hidden is not None)}") in r.stdout
+
+
+def test_build_goes_without_the_native_marshalling(monkeypatch, tmp_path, capsys):
+    from paper_2607_27090_amd import build
+    monkeypatch.setattr(build, "BINDING", str(tmp_path / "_binding.so"))
+    monkeypatch.setenv("CXX", "no-such-compiler")
+    build._compile_binding()
+    assert "not built" in capsys.readouterr().err and not os.listdir(tmp_path)
 
 
 def test_retrieve_well_formed_reaches_the_device_check():
