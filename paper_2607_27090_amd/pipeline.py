@@ -104,6 +104,19 @@ def run_request(buf: RequestBuffers, query, bank, store, block_table, paged_k, p
                pairing=pairing, stream=stream)
 
 
+def _build_workspace(size: int, device) -> torch.Tensor:
+    """The workspace a graph build asks for, or as much of it as the GPU has
+    left: a build takes smaller batches in less, down to a quarter or so (and
+    refuses what is too little)."""
+    while True:
+        try:
+            return torch.empty(size, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            if size <= 1 << 20:
+                raise
+            size = size // 16 * 15
+
+
 class AnnIndex:
     """Proximity graph of one bank with the search's seeds (built on the
     device by is_ann_build), and cached search workspaces."""
@@ -119,8 +132,7 @@ class AnnIndex:
         self.fwd = torch.empty(n, degree, dtype=torch.int32, device=dev) if keep_forward else None
         self.seed_ids = torch.empty(self.n_seeds, dtype=torch.int32, device=dev)
         self.seed_bank = torch.empty(self.n_seeds, d, dtype=bank.dtype, device=dev)
-        ws = torch.empty(is_ann_build_workspace_size(n, d, degree, self.dtype), dtype=torch.uint8,
-                         device=dev)
+        ws = _build_workspace(is_ann_build_workspace_size(n, d, degree, self.dtype), dev)
         is_ann_build(bank, n, d, degree, self.graph, n_seeds=self.n_seeds, fwd=self.fwd,
                      seed_ids=self.seed_ids, seed_bank=self.seed_bank, workspace=ws,
                      stream=stream)

@@ -63,6 +63,27 @@ def test_build_goes_without_the_native_marshalling(monkeypatch, tmp_path, capsys
     assert "not built" in capsys.readouterr().err and not os.listdir(tmp_path)
 
 
+def test_build_workspace_takes_what_is_left(monkeypatch):
+    # the graph build's workspace asks for large batches; with less memory left it
+    # gets close to all of that
+    from paper_2607_27090_amd import pipeline
+    left = {"bytes": 0}
+    empty = torch.empty
+
+    def limited(size, **kw):
+        if size > left["bytes"]:
+            raise torch.OutOfMemoryError("out of memory")
+        return empty(size, **kw)
+
+    monkeypatch.setattr(torch, "empty", limited)
+    for left["bytes"] in (900 << 20, 300 << 20, 40 << 20):
+        got = pipeline._build_workspace(900 << 20, "cpu").numel()
+        assert 0.9 * left["bytes"] <= got <= left["bytes"]
+    left["bytes"] = 0
+    with pytest.raises(torch.OutOfMemoryError):
+        pipeline._build_workspace(900 << 20, "cpu")
+
+
 def test_retrieve_well_formed_reaches_the_device_check():
     with pytest.raises(ValueError, match="device tensors"):
         call_retrieve(retrieve_args())
