@@ -119,7 +119,7 @@ bool fused_applies(int64_t n, int32_t d, int32_t nq, int64_t bank_stride, int32_
 // scores (0: none). `plan`: see enqueue_retrieve.
 int dense_tile_rows(int64_t n, int32_t d, int32_t plan, int64_t bank_stride, int32_t dtype) {
     if (is::scan_direct_applies(n, d, plan, bank_stride, dtype))
-        return is::scan_direct_tile_rows(n, plan);
+        return is::scan_direct_tile_rows(n, plan, dtype);
     return is::scan_mfma_applies(n, d, plan, bank_stride, dtype) ? is::mfma_tile_rows() : 0;
 }
 

@@ -42,7 +42,7 @@ hipError_t launch_scan_mfma_filter(const void* query, const void* bank, int d, i
 // scan_direct_tile_rows() rows, as order bits, tmax[q][tiles]. Tile and sums are
 // those for `plan` queries, whatever nq.
 bool scan_direct_applies(int64_t n, int d, int nq, int64_t bank_stride, int dtype);
-int scan_direct_tile_rows(int64_t n, int plan);
+int scan_direct_tile_rows(int64_t n, int plan, int dtype);
 hipError_t launch_scan_direct(const void* query, const void* bank, int64_t n, int d, int nq,
                               int plan, int dtype, float* scores, uint32_t* tmax, hipStream_t st);
 int64_t select_chunk_len();
