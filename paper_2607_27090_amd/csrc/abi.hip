@@ -200,7 +200,7 @@ int enqueue_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t
     e = direct ? is::launch_scan_direct(query_emb, bank, n, d, nq, plan, dtype, scores, tmax, st)
         : mfma
             ? is::launch_scan_mfma(query_emb, bank, d, nq, 0, n, scores, n, tmax, st)
-            : is::launch_scan(query_emb, bank, n, d, nq, bank_stride, dtype, scores, st);
+            : is::launch_scan(query_emb, bank, n, d, nq, plan, bank_stride, dtype, scores, st);
     if (e != hipSuccess) return fail(IS_ERR_HIP, "scan launch: %s", hipGetErrorString(e));
     if (tmax) {
         e = is::launch_select_tiles(scores, tmax, n, dense_tile_rows(n, d, plan, bank_stride, dtype),

@@ -14,7 +14,8 @@ namespace is {
 int compute_units();
 
 // retrieve.hip
-hipError_t launch_scan(const void* query, const void* bank, int64_t n, int d, int nq,
+bool scan_few_scores(int64_t n, int d, int nq, int dtype);
+hipError_t launch_scan(const void* query, const void* bank, int64_t n, int d, int nq, int plan,
                        int64_t bank_stride, int dtype, float* scores, hipStream_t st);
 bool scan_mfma_applies(int64_t n, int d, int nq, int64_t bank_stride, int dtype);
 // Blocks and rows per block of a matrix-core scan of nq queries over `rows` rows (at most

@@ -100,8 +100,9 @@ __device__ __forceinline__ uint4 load_stream(const uint4* p) {
 constexpr int kScanMaxRows = 1024;  // rows per block at most
 
 // One block = 4 waves. blockIdx.y selects a group of NQB queries (shared
-// bank) or one query and its own bank (per-query banks, NQB == 1).
-template <class Tag, int CPL, int NQB, int RB>
+// bank) or one query and its own bank (per-query banks, NQB == 1). WIDE
+// (NQB == 1): 16-byte units are summed in binary64.
+template <class Tag, int CPL, int NQB, int RB, bool WIDE>
 __global__ __launch_bounds__(256) void scan_kernel(const uint4* __restrict__ query,
                                                    const uint4* __restrict__ bank, int64_t n,
                                                    int chunks, int nq, int64_t bank_stride_chunks,
@@ -130,6 +131,18 @@ __global__ __launch_bounds__(256) void scan_kernel(const uint4* __restrict__ que
     // sum of RB rows x NQB queries, reduced across the wave; the lanes whose
     // low bits are zero hand (query, row offset, score) to put()
     auto reduce_rows = [&](uint4 (&v)[RB][CPL], auto&& put) {
+        if constexpr (WIDE) {
+            static_assert(NQB == 1, "one query per block");
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                double s = 0.0;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) s += (double)dot16_acc(v[rb][c], qr[0][c], 0.f, Tag{});
+                s = wave_sum_f64(s);
+                if (lane == 0) put(0, rb, (float)s);
+            }
+            return;
+        }
         float part[NQB * RB];
 #pragma unroll
         for (int qq = 0; qq < NQB; ++qq)
@@ -253,7 +266,7 @@ __global__ __launch_bounds__(256) void scan_kernel(const uint4* __restrict__ que
     }
 }
 
-template <class Tag, int CPL, int NQB>
+template <class Tag, int CPL, int NQB, bool WIDE = false>
 static hipError_t launch_scan_t(const void* query, const void* bank, int64_t n, int chunks, int nq,
                                 int64_t bank_stride_chunks, float* scores, hipStream_t st) {
     constexpr int RB = (CPL <= 2) ? 4 : (CPL <= 4 ? 2 : 1);
@@ -271,13 +284,27 @@ static hipError_t launch_scan_t(const void* query, const void* bank, int64_t n, 
     if (rpb > 1024) rpb = 1024;
     const int64_t gx = (n + rpb - 1) / rpb;
     dim3 grid((unsigned)gx, (unsigned)groups);
-    hipLaunchKernelGGL((scan_kernel<Tag, CPL, NQB, RB>), grid, dim3(256), 0, st,
+    hipLaunchKernelGGL((scan_kernel<Tag, CPL, NQB, RB, WIDE>), grid, dim3(256), 0, st,
                        (const uint4*)query, (const uint4*)bank, n, chunks, nq, bank_stride_chunks,
                        (int)rpb, scores);
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const void* query, const void* bank, int64_t n, int d, int nq,
+// Several queries on one bank, so few scores that the direct scan's chain of
+// steps over a row, 0.6 us per KiB, takes longer than reading every row again
+// for each query (past what a block of the row scan serves in one pass, and
+// eight of fp32 rows up to 4 KiB in two). us per retrieval, direct and row scan:
+// fp32, 250 rows x 2 queries, d = 1,536 11.0 / 7.8, 8,192 27.9 / 11.0; 1,200 x 3,
+// 4,096 18.9 / 13.9; bf16 600 x 3, 4,096 10.1 / 8.4. Past the lines: fp32 250 x 16,
+// 8,192 28.3 / 30.6; 3,000 x 2, 4,096 19.5 / 21.4; bf16 250 x 24, 8,192 12.5 / 18.2.
+bool scan_few_scores(int64_t n, int d, int nq, int dtype) {
+    const int row = d * (dtype == IS_DTYPE_F32 ? 4 : 2);
+    if (nq > 16 || n * nq > (row > 16384 ? 2500 : 4000)) return false;
+    if (row > 4096) return true;
+    return dtype == IS_DTYPE_F32 && row > 2048 && nq > 4 && !(nq <= 8 && n <= 2048);
+}
+
+hipError_t launch_scan(const void* query, const void* bank, int64_t n, int d, int nq, int plan,
                        int64_t bank_stride, int dtype, float* scores, hipStream_t st) {
     const int esz = dtype == 0 ? 4 : 2;
     const int chunks = d * esz / 16;
@@ -285,13 +312,20 @@ hipError_t launch_scan(const void* query, const void* bank, int64_t n, int d, in
     const int cpl = (chunks + kWave - 1) / kWave;
     // A shared bank serves several queries per block so each loaded row is
     // reused from registers: 8 queries while a row takes <= 2 loads per lane
-    // (fp32 only), 4 while it takes <= 4; every other batch of queries on one
-    // bank goes to the matrix cores (scan_direct_applies).
+    // (fp32 only), 4 while it takes <= 4; few scores of longer rows, and of more
+    // queries than that, one query per block, with sums as close as the matrix
+    // cores' compensated ones. Every other batch of queries on one bank goes to
+    // the matrix cores (scan_direct_applies).
     const bool multi = bsc == 0 && nq > 1;
+    const bool wide = bsc == 0 && plan > 1 && scan_few_scores(n, d, plan, dtype);
 #define IS_SCAN_T(TAG, CPL, NQB) \
     return launch_scan_t<TAG, CPL, NQB>(query, bank, n, chunks, nq, bsc, scores, st)
+#define IS_SCAN_W(TAG, CPL) \
+    return launch_scan_t<TAG, CPL, 1, true>(query, bank, n, chunks, nq, bsc, scores, st)
 #define IS_SCAN(TAG)                                        \
     do {                                                    \
+        if (wide && cpl <= 8) IS_SCAN_W(TAG, 8);            \
+        if (wide && cpl <= 16) IS_SCAN_W(TAG, 16);          \
         if (multi && cpl <= 3) IS_SCAN_T(TAG, 3, 4);        \
         if (multi && cpl <= 4) IS_SCAN_T(TAG, 4, 4);        \
         if (multi) return hipErrorInvalidValue;             \
@@ -303,6 +337,8 @@ hipError_t launch_scan(const void* query, const void* bank, int64_t n, int d, in
         IS_SCAN_T(TAG, 16, 1);                              \
     } while (0)
     if (dtype == 0) {
+        if (wide && cpl <= 4) IS_SCAN_W(F32Tag, 4);
+        if (wide && cpl > 16) IS_SCAN_W(F32Tag, 32);
         if (multi && cpl <= 1) IS_SCAN_T(F32Tag, 1, 8);
         if (multi && cpl <= 2) IS_SCAN_T(F32Tag, 2, 8);
         if (!multi && cpl > 16) IS_SCAN_T(F32Tag, 32, 1);  // rows past 16 KiB
@@ -310,6 +346,7 @@ hipError_t launch_scan(const void* query, const void* bank, int64_t n, int d, in
     }
     IS_SCAN(BF16Tag);
 #undef IS_SCAN_T
+#undef IS_SCAN_W
 #undef IS_SCAN
 }
 

@@ -32,6 +32,23 @@ __device__ __forceinline__ float dot16(uint4 a, uint4 b, BF16Tag) {
     return s;
 }
 
+// s + <a, b> over one 16-byte unit of each operand in binary64 (exact products).
+__device__ __forceinline__ double dot16_f64(uint4 a, uint4 b, double s, F32Tag) {
+    s = fma((double)__uint_as_float(a.x), (double)__uint_as_float(b.x), s);
+    s = fma((double)__uint_as_float(a.y), (double)__uint_as_float(b.y), s);
+    s = fma((double)__uint_as_float(a.z), (double)__uint_as_float(b.z), s);
+    return fma((double)__uint_as_float(a.w), (double)__uint_as_float(b.w), s);
+}
+__device__ __forceinline__ double dot16_f64(uint4 a, uint4 b, double s, BF16Tag) {
+    const uint32_t x[4] = {a.x, a.y, a.z, a.w}, y[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        s = fma((double)bf16_lo(x[i]), (double)bf16_lo(y[i]), s);
+        s = fma((double)bf16_hi(x[i]), (double)bf16_hi(y[i]), s);
+    }
+    return s;
+}
+
 // ---- wave helpers ----------------------------------------------------------
 
 __device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int off) {

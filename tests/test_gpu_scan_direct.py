@@ -74,6 +74,52 @@ def test_direct_scan_scores_are_no_further_off_than_row_sums():
     assert np.linalg.norm(gsc - ex) / np.linalg.norm(ex) < 2.0 ** -24
 
 
+@pytest.mark.parametrize("n,d,nq,dt", [
+    (249, 776, 10, torch.float32), (400, 1024, 10, torch.float32),    # 4 loads per lane
+    (301, 1032, 3, torch.float32), (130, 2048, 9, torch.float32),     # 8
+    (90, 2096, 6, torch.float32), (257, 4096, 2, torch.float32),      # 16
+    (70, 4104, 5, torch.float32), (208, 8192, 12, torch.float32),     # 32
+    (200, 2056, 9, torch.bfloat16), (301, 4096, 2, torch.bfloat16),   # 8 loads per lane
+    (90, 4104, 6, torch.bfloat16), (1, 8192, 16, torch.bfloat16),     # 16
+])
+def test_few_scores_of_long_rows(n, d, nq, dt):
+    # one query per block; the 4 (bf16: 8) products of a unit are added in fp32,
+    # units in binary64
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    bank, q = _unit(n, d, g).to(dt), _unit(nq, d, g).to(dt)
+    gids, gsc = _retrieve(q, bank, n)
+    a, b = q.double(), bank.double()
+    ex, mag = (a @ b.t()).cpu().numpy(), (a.abs() @ b.abs().t()).cpu().numpy()
+    off = size = 0.0
+    for r in range(nq):
+        assert sorted(gids[r].tolist()) == list(range(n)) and (np.diff(gsc[r]) <= 0).all()
+        e = ex[r][gids[r]]
+        assert (np.abs(gsc[r] - e) <= 2.0 ** -24 * (np.abs(e) + 8 * mag[r][gids[r]])).all()
+        off, size = off + np.square(gsc[r] - e).sum(), size + np.square(e).sum()
+    # no further off than one rounding of the sum (2^-24) would be at most
+    assert np.sqrt(off / size) < 2.0 ** -24
+
+
+def test_few_scores_of_long_rows_take_no_longer_than_a_step_chain():
+    # 250 rows of 8,192 fp32 values, two queries: 28 us on the matrix cores, one
+    # step after another over each row, against 9
+    g = torch.Generator(device="cuda").manual_seed(3)
+    long_rows, short_rows = _unit(250, 8192, g), _unit(250, 512, g)
+    us = []
+    for bank in (long_rows, short_rows):
+        q = bank[:2].contiguous()
+        buf = RequestBuffers(n=250, d=bank.shape[1], k=10, nq=2, emb_dtype=bank.dtype, max_tokens=1)
+        buf.retrieve(q, bank)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                buf.retrieve(q, bank)
+        us.append(_us(graph.replay) / 20)
+    log(f"250 x 2, d = 8,192 / 512: {us[0]:.1f} / {us[1]:.1f} us")
+    assert us[0] < 2.2 * us[1]
+
+
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 def test_direct_scan_non_finite_operands(dt):
     g = torch.Generator(device="cuda").manual_seed(8)
