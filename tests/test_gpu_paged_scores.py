@@ -103,11 +103,14 @@ def test_paged_scores_shares(nq, tokens, capacity):
         assert (sc[r, :, n:] == -7.0).all()
 
 
-def test_paged_scores_capacity_costs_nothing():
-    # 4 requests of up to 2,560 tokens in a buffer for them and in one for 131,072
-    # (10 and 209 us where a block's share followed the capacity)
-    bt, pk, q, m = _setup(4, 32, 32, 32, 2560, 16, 0, seed=5)
-    wide = torch.full((4, 131_072 // 16), -1, dtype=torch.int32, device="cuda")
+@pytest.mark.parametrize("tokens,capacity,limit", [
+    (2560, 131_072, 3.0),  # 10 and 209 us where a block's share followed the capacity
+    (100, 4096, 1.4),      # 6.3 and 10.7 where its number of heads did
+])
+def test_paged_scores_capacity_costs_nothing(tokens, capacity, limit):
+    # 4 requests in a buffer for their tokens and in a larger one
+    bt, pk, q, m = _setup(4, 32, 32, 32, tokens, 16, 0, seed=5)
+    wide = torch.full((4, capacity // 16), -1, dtype=torch.int32, device="cuda")
     wide[:, :bt.shape[1]] = bt
 
     def us(bt, tokens):
@@ -118,19 +121,24 @@ def test_paged_scores_capacity_costs_nothing():
                             num_slots=pk.shape[1], max_blocks=bt.shape[1], max_tokens=tokens,
                             rope_theta=THETA)
 
+        call()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                call()
         best = 1e9
         for _ in range(5):
             a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             a.record()
-            for _ in range(20):
-                call()
+            graph.replay()
             b.record()
             torch.cuda.synchronize()
             best = min(best, a.elapsed_time(b) * 50)
         return best
 
-    tight, loose = us(bt, 2560), us(wide, 131_072)
-    assert loose < 3 * tight, (tight, loose)
+    tight, loose = us(bt, tokens), us(wide, capacity)
+    assert loose < limit * tight, (tight, loose)
 
 
 def test_paged_scores_skips_bad_tokens_only():
