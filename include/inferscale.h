@@ -94,8 +94,9 @@ const char* is_version(void);
  * ("" if none). The pointer stays valid until the thread's next call. */
 const char* is_last_error(void);
 
-/* Bytes of device workspace is_retrieve needs for these sizes (0 on bad
- * arguments; *bytes receives the size). Arguments as in is_retrieve. */
+/* Bytes of device workspace with which is_retrieve takes its fastest path for
+ * these sizes (0 on bad arguments; *bytes receives the size). Arguments as in
+ * is_retrieve. */
 int is_retrieve_workspace_size(int64_t n, int32_t d, int32_t k, int32_t nq, int32_t dtype,
                                size_t* bytes);
 
@@ -105,7 +106,7 @@ int is_retrieve_workspace_size(int64_t n, int32_t d, int32_t k, int32_t nq, int3
  * For request r < nq with bank B_r = bank + r * bank_stride elements
  * (bank_stride == 0: every request searches the same bank):
  *   s_j = sum_t query_emb[r][t] * B_r[j][t],  j < n
- * accumulated in fp32 (bf16 inputs: exact bf16 x bf16 products, fp32 sums).
+ * accumulated in fp32 or wider (bf16 inputs: exact bf16 x bf16 products).
  * Output row r lists the k facts with the highest s_j, best first; equal
  * scores go to the lower id; -0.0 counts as +0.0 and NaN as the lowest.
  *
@@ -121,8 +122,11 @@ int is_retrieve_workspace_size(int64_t n, int32_t d, int32_t k, int32_t nq, int3
  *   bank_stride elements between consecutive requests' banks (0 = shared);
  *              a multiple of 8 elements
  *   dtype      IS_DTYPE_F32 or IS_DTYPE_BF16
- *   workspace  device scratch of at least is_retrieve_workspace_size bytes,
- *              256-byte aligned; its contents are not preserved
+ *   workspace  device scratch of is_retrieve_workspace_size bytes, 256-byte
+ *              aligned; its contents are not preserved. Some sizes can do
+ *              with less, more slowly and with the same results: fewer bytes
+ *              than a call must have are refused with IS_ERR_WORKSPACE, whose
+ *              message (is_last_error) says how many those are
  */
 int is_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t d, int32_t k,
                 int32_t* out_ids, float* out_scores, int32_t nq, int64_t bank_stride,
@@ -141,11 +145,12 @@ int is_retrieve(const void* query_emb, const void* bank, int64_t n, int32_t d, i
  * IS_RETRIEVE_NOALLOC_MAX_BYTES in the library's own device memory, one per
  * GPU, held from the first call on that GPU until the process ends; the
  * first call on a GPU looks up that array's device address (no allocation).
- * Sizes whose scratch (is_retrieve_workspace_size) exceeds the array are
+ * Sizes that must have more scratch than the array (the least workspace that
+ * is_retrieve accepts, which can be less than is_retrieve_workspace_size) are
  * refused with IS_ERR_WORKSPACE before anything is enqueued: for example
  * nq * n * 4 bytes of scores must fit (1 query: n up to ~4M; 8 queries over
- * 100,000 facts fit; the filtered matrix-core path for many queries over a
- * large bf16 bank does not).
+ * 100,000 facts fit; many queries over a large bf16 bank, whose surviving
+ * scores take up to 8 bytes for each row and query, do not).
  * Every call on one GPU shares that GPU's array, which keeps the last call's
  * contents: calls that overlap in time on one GPU (on different streams, or
  * from different threads) race and give undefined results. Calls on one
@@ -353,7 +358,9 @@ int is_stream_copy(void* dst, const void* src, size_t bytes, void* stream);
  * for is_retrieve) is higher, or equal with a lower id.
  */
 
-/* Bytes of device workspace is_ann_build needs (0 on bad arguments). */
+/* Bytes of device workspace with which is_ann_build is fastest (0 on bad
+ * arguments): one batch's retrieval, up to 1 GiB where a batch of 256 rows does
+ * with that, and the lists of the whole graph. */
 int is_ann_build_workspace_size(int64_t n, int32_t d, int32_t degree, int32_t dtype,
                                 size_t* bytes);
 
@@ -379,9 +386,12 @@ int is_ann_build_workspace_size(int64_t n, int32_t d, int32_t degree, int32_t dt
  *   fwd        int32 [n][degree] device (output F) or NULL
  *   seed_ids   int32 [n_seeds] device; seed_bank [n_seeds][d] of dtype,
  *              16-byte aligned
- *   workspace  at least is_ann_build_workspace_size bytes, 256-byte aligned
- * Cost: one exact retrieval per batch of 256 bank rows, then O(n * degree)
- * for the reverse edges. Built once per bank, outside the request path
+ *   workspace  is_ann_build_workspace_size bytes, 256-byte aligned. With
+ *              less the batches are smaller and the graph is the same; less
+ *              than a batch of 256 rows must have is refused with
+ *              IS_ERR_WORKSPACE (is_last_error says how much that is)
+ * Cost: one exact retrieval per batch of up to 1,024 bank rows (256 at least),
+ * then O(n * degree) for the reverse edges. Built once per bank, outside the request path
  * (§6.1 counts index construction as offline set-up).
  */
 int is_ann_build(const void* bank, int64_t n, int32_t d, int32_t degree, int32_t dtype,

@@ -60,10 +60,11 @@ inline RowShares row_shares(int64_t rows, int tile, int step, int qtiles, int cu
 // (`parts` of those), about `target` in all at full capacity, so that a large
 // max_tokens costs no blocks. The blocks of a request share out its m placed
 // tokens, in groups of 16: as many groups each as give `target` blocks if every
-// request placed m, or, with m close to the capacity, max_tokens. (With shares by capacity, 300 tokens of 131,072 were one
-// block's work: 32 requests of 32 heads of 32 140 us, by m 14.) The kernel is
-// small, and its first loads wait for its share: with divisions a call took 0.3
-// us longer, so the launch brings reciprocals.
+// request placed m, or, with m close to the capacity, max_tokens. (With shares by
+// capacity, 300 tokens of 131,072 were one block's work: 32 requests of 32 heads
+// of 32 140 us, by m 14.) The kernel is small, and its first loads wait for its
+// share: with divisions a call took 0.3 us longer, so the launch brings
+// reciprocals.
 struct TokenRule {
     uint32_t blocks;
     uint32_t per_block;  // 2^32 / blocks, rounded up

@@ -7,7 +7,8 @@
 //     * scan_kernel, a bandwidth-bound GEMV: each wave streams whole rows
 //       with 16-byte loads, keeps its 1-8 queries in registers and reduces
 //       the per-row partial sums across the wave with a transposing
-//       butterfly, so that V partial sums cost V-1 shuffles;
+//       butterfly, so that V partial sums cost V-1 shuffles (also few scores of
+//       long rows, one query per block);
 //     * scan_direct_kernel (scan_direct.hip: more queries on one bank than
 //       that kernel serves in a pass, small and medium products);
 //     * scan_mfma_kernel (larger ones, 32 or more queries against one bf16 bank):
@@ -22,7 +23,8 @@
 //     whose sorted k winners are merged by rank (each key's position in its
 //     list plus binary searches in the others), or, beyond that kernel's
 //     size, ranked again in chunks of keys (the smallest of k group maxima
-//     bounds those); the survivors of the filtered matrix-core scan are
+//     bounds those); rows whose scan wrote tile maxima are ranked from those
+//     (select_tiles_kernel); the survivors of the filtered matrix-core scan are
 //     ranked by select_regions_kernel. Ties go to the lower id (score desc,
 //     id asc).
 #include <algorithm>
