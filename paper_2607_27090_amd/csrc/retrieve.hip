@@ -294,16 +294,17 @@ static hipError_t launch_scan_t(const void* query, const void* bank, int64_t n, 
 
 // Several queries on one bank, so few scores that the direct scan's chain of
 // steps over a row, 0.6 us per KiB, takes longer than reading every row again
-// for each query (past what a block of the row scan serves in one pass, and
-// eight of fp32 rows up to 4 KiB in two). us per retrieval, direct and row scan:
-// fp32, 250 rows x 2 queries, d = 1,536 11.0 / 7.8, 8,192 27.9 / 11.0; 1,200 x 3,
-// 4,096 18.9 / 13.9; bf16 600 x 3, 4,096 10.1 / 8.4. Past the lines: fp32 250 x 16,
-// 8,192 28.3 / 30.6; 3,000 x 2, 4,096 19.5 / 21.4; bf16 250 x 24, 8,192 12.5 / 18.2.
+// for each query (past what a block of the row scan serves in one pass, or eight
+// of fp32 rows up to 4 KiB in two). us per retrieval, direct and row scan: fp32,
+// 250 rows x 2 queries, d = 1,536 11.0 / 7.8, 8,192 27.9 / 11.0; 1,200 x 3, 4,096
+// 18.9 / 13.9; bf16 600 x 3, 4,096 10.1 / 8.4; fp32 400 x 16, 1,024 10.1 / 9.1, 600 x
+// 12, 640 9.8 / 9.3. Past the lines: fp32 250 x 16, 8,192 28.3 / 30.6; 3,000 x 2,
+// 4,096 19.5 / 21.4; bf16 250 x 24, 8,192 12.5 / 18.2; fp32 1,000 x 9, 1,024 10.5 / 11.7.
 bool scan_few_scores(int64_t n, int d, int nq, int dtype) {
     const int row = d * (dtype == IS_DTYPE_F32 ? 4 : 2);
-    if (nq > 16 || n * nq > (row > 16384 ? 2500 : 4000)) return false;
-    if (row > 4096) return true;
-    return dtype == IS_DTYPE_F32 && row > 2048 && nq > 4 && !(nq <= 8 && n <= 2048);
+    if (row <= 4096)
+        return dtype == IS_DTYPE_F32 && row > 2048 && nq > 8 && nq <= 32 && n * nq <= 8000;
+    return nq <= 16 && n * nq <= (row > 16384 ? 2500 : 4000);
 }
 
 hipError_t launch_scan(const void* query, const void* bank, int64_t n, int d, int nq, int plan,

@@ -75,7 +75,8 @@ def test_direct_scan_scores_are_no_further_off_than_row_sums():
 
 
 @pytest.mark.parametrize("n,d,nq,dt", [
-    (249, 776, 10, torch.float32), (400, 1024, 10, torch.float32),    # 4 loads per lane
+    (249, 776, 10, torch.float32), (250, 520, 32, torch.float32),     # 4 loads per lane
+    (888, 1024, 9, torch.float32),
     (301, 1032, 3, torch.float32), (130, 2048, 9, torch.float32),     # 8
     (90, 2096, 6, torch.float32), (257, 4096, 2, torch.float32),      # 16
     (70, 4104, 5, torch.float32), (208, 8192, 12, torch.float32),     # 32
