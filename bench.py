@@ -839,12 +839,12 @@ def _short_kernel(name):
 
 def _source_hashes():
     """Digests of the sources the inject launch is built from (its kernel,
-    the shared device helpers, the launch shapes and declarations, the ABI layer):
+    the shared device helpers, the launcher declarations and the ABI layer):
     a summary stops applying once any of them changes."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_2607_27090_amd", "csrc")
     out = []
-    for name in ("abi.hip", "common.hpp", "grid.hpp", "inject.hip", "launch.hpp"):
+    for name in ("abi.hip", "common.hpp", "inject.hip", "launch.hpp"):
         with open(os.path.join(csrc, name), "rb") as f:
             out.append(f"{name} {hashlib.sha256(f.read()).hexdigest()}")
     return " ".join(out)
