@@ -74,6 +74,23 @@ def test_direct_scan_scores_are_no_further_off_than_row_sums():
     assert np.linalg.norm(gsc - ex) / np.linalg.norm(ex) < 2.0 ** -24
 
 
+@pytest.mark.parametrize("d", [40, 64, 72, 88, 128])
+def test_short_rows_are_no_further_off_than_row_sums(d):
+    # one or two steps of few matrix ops; a single query takes the row scan
+    g = torch.Generator(device="cuda").manual_seed(d)
+    n, nq, k, off = 20_000, 13, 512, [0.0, 0.0]
+    for _ in range(4):
+        bank, q = _unit(n, d, g).bfloat16(), _unit(nq, d, g).bfloat16()
+        ex = (q.double() @ bank.double().t()).cpu().numpy()
+        batch = _retrieve(q, bank, k)
+        for r in range(nq):
+            single = _retrieve(q[r:r + 1], bank, k)
+            for i, (ids, sc) in enumerate(((batch[0][r], batch[1][r]), (single[0][0], single[1][0]))):
+                off[i] += np.square(sc - ex[r][ids]).sum()
+    log(f"d = {d}: {off[0] ** 0.5:.3e}, row sums {off[1] ** 0.5:.3e}")
+    assert off[0] <= off[1]
+
+
 @pytest.mark.parametrize("n,d,nq,dt", [
     (249, 776, 10, torch.float32), (250, 520, 32, torch.float32),     # 4 loads per lane
     (888, 1024, 9, torch.float32),
