@@ -74,6 +74,33 @@ def test_direct_scan_scores_are_no_further_off_than_row_sums():
     assert np.linalg.norm(gsc - ex) / np.linalg.norm(ex) < 2.0 ** -24
 
 
+@pytest.mark.parametrize("n", [40_001, 40_002, 40_003])
+def test_dense_tiles_write_rows_of_any_length(n):
+    # score rows that are no multiples of 16 bytes, the last one up to its end
+    g = torch.Generator(device="cuda").manual_seed(n)
+    bank, q = _unit(n, 64, g).bfloat16(), _unit(160, 64, g).bfloat16()
+    q[-1] = bank[-1]
+    _check(q, bank, 10)
+
+
+def test_dense_tiles_rows_of_any_length_take_no_longer():
+    # 256 queries over 40,000 and 40,001 rows: 29 and 31 us (55 score by score)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    us = []
+    for n in (40_000, 40_001):
+        bank, q = _unit(n, 64, g).bfloat16(), _unit(256, 64, g).bfloat16()
+        buf = RequestBuffers(n=n, d=64, k=10, nq=256, emb_dtype=bank.dtype, max_tokens=1)
+        buf.retrieve(q, bank)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                buf.retrieve(q, bank)
+        us.append(_us(graph.replay) / 20)
+    log(f"256 x 40,000 / 40,001: {us[0]:.1f} / {us[1]:.1f} us")
+    assert us[1] < 1.4 * us[0]
+
+
 @pytest.mark.parametrize("d", [40, 64, 72, 88, 128])
 def test_short_rows_are_no_further_off_than_row_sums(d):
     # one or two steps of few matrix ops; a single query takes the row scan
